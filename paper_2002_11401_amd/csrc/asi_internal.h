@@ -38,6 +38,19 @@ constexpr int kMaxRelaxWaves = 16;
 // max tree, so the relax never speculates.
 constexpr int kSpecMaxD = 128;
 
+// Most magnets whose relax keys are held in LDS (4 bytes each: 147,456 of the
+// 163,840 bytes, beside a spin bit per magnet and the workgroup's own state).
+constexpr int64_t kLdsMaxN = 36864;
+// Default of asi_tuning.spec_min.
+constexpr int64_t kSpecMinDefault = 32;
+
+// The relax of an instance, each path a kernel of its own.
+enum RelaxPath : int32_t {
+  kPathTree = 0,  // max tree
+  kPathSpec = 1,  // speculative batches or the max tree, by step
+  kPathLds = 2,   // one flip at a time, every key in LDS
+};
+
 // How the dipolar sum of a row is obtained at the start of a field step.
 enum FieldMode : int32_t {
   kFieldCarry = 0,  // gathered once, then carried across steps by the flip deltas
@@ -95,7 +108,7 @@ struct InstDev {
   // chunks: [nch][n] (easy, hard); null and nch == 0 when not allocated
   ASI_GLOBAL double2* part;
   int32_t nch;
-  int32_t pad1;
+  int32_t lds_keys;       // relaxed on kPathLds (see relax_keys_in_lds)
   ASI_GLOBAL int32_t* log_t;         // flip log
   ASI_GLOBAL int32_t* log_j;
   int64_t log_cap;
@@ -218,24 +231,31 @@ constexpr int64_t kHdSplitSlices = 256;
 // relax structures of every paused one.
 void launch_field(const InstDev* insts, RunDev* runs, const int32_t* blk_inst,
                   const int32_t* blk_row0, int64_t nblocks, hipStream_t st);
-// One workgroup per instance: relax the current step.  tree_only when no
-// instance of the launch may speculate (see relax_may_speculate): the kernel
-// then holds the max tree alone.
-void launch_relax(const InstDev* insts, RunDev* runs, int32_t count, int32_t waves,
-                  size_t lds_bytes, bool tree_only, hipStream_t st);
 // Whether an instance of degree D relaxed by workgroups of `waves` wavefronts
 // may take the speculative path (it needs the full 16-wavefront workgroup).
 inline bool relax_may_speculate(int32_t D, int32_t waves) {
   return waves == kMaxRelaxWaves && D <= kSpecMaxD;
 }
-// One workgroup per instance: up to max_steps whole steps (field phase and
-// relax) per instance.  With budget_ticks > 0 a workgroup stops once that many ticks of the
+// Whether it is relaxed one flip at a time with every key in LDS: where they
+// fit (a thread owns at most 64 magnets), unless the caller asked for
+// speculation from a number of flippable magnets that it can reach.
+inline bool relax_keys_in_lds(int64_t n, int32_t D, int32_t waves, int64_t spec_min) {
+  return n <= kLdsMaxN && n <= (int64_t)64 * 64 * waves &&
+         (spec_min == kSpecMinDefault || spec_min > n || !relax_may_speculate(D, waves));
+}
+// One workgroup per instance: relax the current step of the instances on
+// `path` (kPathTree only where no other instance of the table may speculate).
+void launch_relax(const InstDev* insts, RunDev* runs, int32_t count, int32_t waves,
+                  size_t lds_bytes, RelaxPath path, hipStream_t st);
+// One workgroup per instance, of those on kPathLds or of the others: up to
+// max_steps whole steps (field phase and relax) per instance.  With
+// budget_ticks > 0 a workgroup stops once that many ticks of the
 // device's constant-rate clock have passed: between steps, or inside a relax
 // (which then pauses, see RunDev).  With first_ready a field launch has just
 // computed each active instance's fields and rebuilt each paused one's relax
 // structures.
 void launch_fused(const InstDev* insts, RunDev* runs, int32_t count, int32_t waves,
-                  size_t lds_bytes, int64_t max_steps, int64_t budget_ticks,
+                  size_t lds_bytes, RelaxPath path, int64_t max_steps, int64_t budget_ticks,
                   int32_t first_ready, hipStream_t st);
 // Run-cursor update on the stream; with ccount, also empties the
 // instance's candidate pool.
@@ -244,8 +264,10 @@ void launch_set_run(RunDev* run, int32_t* ccount, int64_t t, int64_t t_end, int3
 // RunDev::status of a step whose candidate pool overflowed its capacity
 // (an internal error: the host reports ASI_EDEVICE).
 constexpr int32_t kPoolOverflow = -3;
-// Dynamic LDS of the relax and fused kernels for an instance of n magnets.
+// Dynamic LDS of the relax and fused kernels for an instance of n magnets: of
+// the tree and speculative paths, and of kPathLds.
 size_t relax_lds_bytes(int64_t n, int32_t l1_shift);
+size_t relax_keys_lds_bytes(int64_t n, int32_t waves);
 int32_t relax_l1_shift(int64_t n);
 // Raise the dynamic-LDS limit of the relax kernels (call once per process).
 hipError_t configure_kernels();

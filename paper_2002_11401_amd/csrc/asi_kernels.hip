@@ -21,6 +21,7 @@
 #include <algorithm>
 #include <climits>
 #include <mutex>
+#include <utility>
 
 #define ASI_KERNELS_UNIT 1
 #include "asi_internal.h"
@@ -110,6 +111,82 @@ __device__ inline double switching_key(int s, double hp, double hq, double hk, d
   return key_from_powers(a, q, ep, eq);
 }
 
+// The exact key for the rare lanes of a relax that need it: out of line, so
+// that the FP64 powers' registers and constants stay out of the relax loop.
+__device__ __attribute__((noinline)) double switching_key_far(int s, double hp, double hq,
+                                                              double hk, double b, double c,
+                                                              double ep, double eq) {
+  return switching_key(s, hp, hq, hk, b, c, ep, eq);
+}
+
+// Single-precision code of a key: the float bits of an approximation k of
+// Eq. 5's left-hand side (positive floats order like their bits) with the two
+// lowest bits replaced by flags; 0 when the magnet certainly cannot flip.
+// k is within kCodeRel of the FP64 key (of the left-hand side, where that is
+// at most 1):
+//   - the normalised components are formed in FP64 and rounded once, 2^-24;
+//   - v_log_f32 and v_exp_f32 are within an ulp.  With exponents e in
+//     [1/4, 4] and k < 16, |e log2 x| <= 4 for the term that matters, so its
+//     error is below 4 * 2^-22 + 4 * (1.45 * 2^-24 + 2^-24) = 1.54e-6, the
+//     term's relative error below 1.54e-6 * ln 2 + 2^-23 and the sum's below
+//     1.3e-6 < 2^-19 (a small term errs less against the sum);
+//   - a component that underflows loses a term below (2^-126)^(1/4).
+// Measured over 3e9 random fields and parameters of those ranges: 6.9e-7 at
+// most.  Outside them (of the parameters: fast == false; of a lane: k or h_k)
+// the FP64 key itself is rounded.
+constexpr float kCodeRel = 0x1p-19f;
+// Codes at least this far below a code belong to keys certainly below its
+// key: approximations whose ratio is below 1 - 2 kCodeRel, that is at most
+// 2 * 2^-19 * 2^24 = 64 units in the last place, and the flags and roundings.
+constexpr uint32_t kCodeNear = 76;
+// From here the key is certainly above 1 (kCodeRel is 16 units above 1).
+constexpr uint32_t kCodeSure = 0x3f800000u + 40u;
+constexpr uint32_t kCodeDown = 1u;   // flag: the spin is -1
+constexpr uint32_t kCodeExact = 2u;  // flag: the key array holds the FP64 key
+
+struct KeyPar {
+  double b, c, ep, eq;   // Eq. 5 in FP64
+  double ib, ic;
+  float fep, feq;
+  bool fast;             // the approximation's error bound holds
+};
+
+__device__ inline KeyPar key_par(const InstDev* __restrict__ I) {
+  KeyPar P;
+  P.b = I->b;
+  P.c = I->c;
+  P.ep = I->e_par;
+  P.eq = I->e_perp;
+  P.ib = 1.0 / P.b;
+  P.ic = 1.0 / P.c;  // 0 for c = infinity: no hard-axis term
+  P.fep = (float)P.ep;
+  P.feq = (float)P.eq;
+  P.fast = P.ep >= 0.25 && P.ep <= 4.0 && P.eq >= 0.25 && P.eq <= 4.0 && P.b > 0x1p-60 &&
+           P.b < 0x1p60 && P.c > 0x1p-60 && (P.c < 0x1p60 || P.ic == 0.0);
+  return P;
+}
+
+// Code of an FP64 key (keys past the range of a float share the largest
+// code), with the spin's flag.
+__device__ inline uint32_t code_of_key(double key, bool neg) {
+  if (!(key > 0.0)) return 0u;
+  return (__float_as_uint((float)fmin(key, 0x1p127)) & ~3u) | (neg ? kCodeDown : 0u);
+}
+
+__device__ inline uint32_t key_code(bool neg, double hp, double hq, double hk, const KeyPar& P) {
+  const float fk = (float)hk;
+  const double r0 = (double)__builtin_amdgcn_rcpf(fk);
+  const double r = __builtin_fma(__builtin_fma(-hk, r0, 1.0), r0, r0);  // 1 / h_k
+  const float a = (float)(fabs(hp) * r * P.ib);
+  const float q = (float)(fabs(hq) * r * P.ic);
+  const float k = __builtin_amdgcn_exp2f(P.fep * __builtin_amdgcn_logf(a)) +
+                  __builtin_amdgcn_exp2f(P.feq * __builtin_amdgcn_logf(q));
+  const bool against = neg ? hp > 0.0 : hp < 0.0;
+  if (__builtin_expect(against && !(P.fast && k < 16.0f && fk > 0x1p-60f && fk < 0x1p60f), 0))
+    return code_of_key(switching_key_far(neg ? -1 : 1, hp, hq, hk, P.b, P.c, P.ep, P.eq), neg);
+  return against && k > 1.0f - kCodeRel ? (__float_as_uint(k) & ~3u) | (neg ? kCodeDown : 0u) : 0u;
+}
+
 // Eq. 3 for a unit source moment mhat_s at (sx, sy) seen at (fx, fy),
 // projected on the observer's easy axis (A) and hard axis (B);
 // mhatperp = (-my, mx).  A is symmetric in (f, s) bit for bit: swapping
@@ -159,6 +236,25 @@ __device__ inline double wave_max_f64(double v) {
   const double r0 = readlane_f64(v, 0), r1 = readlane_f64(v, 16);
   const double r2 = readlane_f64(v, 32), r3 = readlane_f64(v, 48);
   return fmax(fmax(r0, r1), fmax(r2, r3));
+}
+
+// Maximum of an unsigned value over each row of 16 lanes, in every lane.
+__device__ inline uint32_t row_max_u32(uint32_t v) {
+  v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xF, 0xF, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x140, 0xF, 0xF, false));
+  return v;
+}
+
+// Maximum over the 64 lanes, uniform.
+__device__ inline uint32_t wave_max_u32(uint32_t v) {
+  v = row_max_u32(v);
+  const uint32_t r0 = (uint32_t)__builtin_amdgcn_readlane((int)v, 0);
+  const uint32_t r1 = (uint32_t)__builtin_amdgcn_readlane((int)v, 16);
+  const uint32_t r2 = (uint32_t)__builtin_amdgcn_readlane((int)v, 32);
+  const uint32_t r3 = (uint32_t)__builtin_amdgcn_readlane((int)v, 48);
+  return max(max(r0, r1), max(r2, r3));
 }
 
 // Wave-wide argmax of (key, payload) where lane order is index order:
@@ -431,17 +527,21 @@ __device__ __forceinline__ double field_finish(const InstDev* __restrict__ I, in
   return key;
 }
 
-// Key of row i as the state holds it, for an instance whose relax paused
-// mid-step: the relax keeps every key exact, so its candidate structures
-// are rebuilt from the key array instead of a field evaluation.
+// Key of row i for an instance whose relax paused mid-step: the relax keeps
+// every field exact, so the key is that of the stored field (bit for bit the
+// key an uninterrupted relax would hold).
 __device__ __forceinline__ double stored_key(const InstDev* __restrict__ I, int64_t i,
                                              uint32_t& payload) {
-  payload = (uint32_t)i | (I->s[i] < 0 ? 0x80000000u : 0u);
-  return I->key[i];
+  const int si = I->s[i];
+  const double2 h = I->h[i];
+  const double key = switching_key(si, h.x, h.y, I->hk[i], I->b, I->c, I->e_par, I->e_perp);
+  I->key[i] = key;
+  payload = (uint32_t)i | (si < 0 ? 0x80000000u : 0u);
+  return key;
 }
 
 // Field phase for the 64 rows starting at row0 (a multiple of 64), by one
-// wavefront: rows (or, resuming a paused relax, their stored keys), then
+// wavefront: rows (or, resuming a paused relax, the keys of their stored fields), then
 // their maximum key into the per-64-row table.  Returns the lane's (key,
 // payload) for the candidate pool.
 __device__ __forceinline__ double field_rows64(const InstDev* __restrict__ I, int64_t row0,
@@ -2059,6 +2159,247 @@ __device__ __forceinline__ int relax_tree(const InstDev* __restrict__ I, int64_t
   return status;
 }
 
+// ------------------------------------------------------------ relax, keys in LDS
+// One-at-a-time relax for instances whose keys fit in LDS (kLdsMaxN magnets):
+// the code of every magnet, a spin bit per magnet, and per wavefront the best
+// code of the magnets its threads own.
+__host__ __device__ inline int flip_tile_shift(int64_t n, int threads) {
+  int sh = 2;
+  while (((int64_t)threads << sh) < n) ++sh;
+  return sh;
+}
+
+__host__ __device__ inline size_t flip_lds_bytes(int64_t n, int threads) {
+  const int sh = flip_tile_shift(n, threads);
+  const size_t tiles = (size_t)((n + (1LL << sh) - 1) >> sh);
+  return (tiles << sh) * 4 + align16((size_t)((n + 31) / 32) * 4) + (size_t)threads * 4;
+}
+
+struct FlipShared {
+  uint4 best[kMaxRelaxWaves];  // per wavefront: code, index, codes near it
+  double rk[kMaxRelaxWaves];   // resolving a near-tie: per wavefront exact key and index
+  uint32_t ri[kMaxRelaxWaves];
+  int pause;
+};
+
+// A global load at a 32-bit byte offset from a uniform base.
+template <class T>
+__device__ __forceinline__ T load_at(const ASI_GLOBAL T* base, uint32_t bytes) {
+  return *(const ASI_GLOBAL T*)((const ASI_GLOBAL char*)base + bytes);
+}
+template <class T>
+__device__ __forceinline__ void store_at(ASI_GLOBAL T* base, uint32_t bytes, T v) {
+  *(ASI_GLOBAL T*)((ASI_GLOBAL char*)base + bytes) = v;
+}
+
+// Relax at step t, one flip at a time.  Each thread owns a tile of
+// consecutive magnets and keeps its largest code in a register.  Per flip:
+//   - the wavefronts' best codes give the winner.  If no other code lies
+//     within kCodeNear of it, and it is surely above 1, it is the magnet the
+//     exact keys would pick; else the exact FP64 keys of the codes that near
+//     decide (keys of 0 are struck out, equal keys go to the lower index);
+//     an exact key is kept in the key array until the magnet's field changes;
+//   - the threads update the neighbours' fields and codes;  [barrier]
+//   - the owners of changed tiles rescan them in LDS and their wavefronts
+//     renew their best.  [barrier]
+// What bounds it: one dependent chain per flip -- the flipped magnet's row,
+// then its neighbours' fields (two round trips to memory), two barriers and
+// four LDS round trips.  Against the max tree it leaves out of that chain the
+// FP64 powers (~200 dependent instructions each; exact keys are evaluated for
+// 1-8 % of the flips), the rescans of tiles in memory and three of five
+// barriers: per flip 6.2 -> 2.1 us on a 5,100-magnet anneal at 632
+// neighbours, 5.6 -> 2.6 on a 20,200-magnet reversal at 632, 5.1 -> 2.2 on a
+// 29,040-magnet reversal at 60; with every key tied (no disorder) 5.1 -> 2.0.
+// Returns as relax_tree.
+__device__ __forceinline__ int relax_lds(const InstDev* __restrict__ I, int64_t t, unsigned char* lds_raw,
+                                         FlipShared& sh, int64_t ncand, int64_t& flips,
+                                         int64_t& logpos, uint64_t& hash, uint64_t deadline) {
+  if (ncand == 0) return 0;  // nothing can flip
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int NT = blockDim.x;
+  const int32_t n = (int32_t)I->n;
+  const int ts = flip_tile_shift(n, NT);
+  const int per = 1 << ts, nc = per >> 2;
+  const int32_t npad = ((n + per - 1) >> ts) << ts;
+  uint32_t* const code = (uint32_t*)lds_raw;
+  uint32_t* const spin = code + npad;  // bit per magnet: spin -1
+  // per thread: a code of its tile changed
+  uint32_t* const touched = (uint32_t*)((unsigned char*)spin + align16((size_t)((n + 31) / 32) * 4));
+
+  const int32_t D = I->D;
+  const int32_t mode = I->field_mode;
+  const KeyPar P = key_par(I);
+  const int64_t max_flips = I->max_flips;
+  const int64_t flips0 = flips;
+
+  for (int q = tid; q < npad / 4; q += NT) ((uint4*)code)[q] = make_uint4(0u, 0u, 0u, 0u);
+  // sign bits of 32 spins per word, from four 8-byte loads (the array's
+  // allocation is a multiple of 256 bytes)
+  for (int q = tid; q < (n + 31) / 32; q += NT) {
+    const ASI_GLOBAL uint64_t* s8 = (const ASI_GLOBAL uint64_t*)I->s + 4 * (int64_t)q;
+    uint64_t v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = (8 * (4 * q + u) < n) ? s8[u] : 0ull;
+    uint32_t w = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      w |= (uint32_t)((((v[u] >> 7) & 0x0101010101010101ull) * 0x0102040810204080ull) >> 56) << (8 * u);
+    spin[q] = w;
+  }
+  touched[tid] = 0u;
+  if (tid < kMaxRelaxWaves) sh.best[tid] = make_uint4(0u, 0u, 0u, 0u);
+  if (tid == 0) sh.pause = 0;
+  __syncthreads();
+  // the field phase's list of flippable magnets, whose keys it also stored
+  for (int64_t q = tid; q < ncand; q += NT) {
+    const uint32_t pay = I->cpay[0][q];
+    const uint32_t i = pay & 0x7fffffffu;
+    code[i] = code_of_key(I->ckey[0][q], (pay >> 31) != 0u) | kCodeExact;
+    touched[i >> ts] = 1u;
+  }
+  __syncthreads();
+
+  int status = 0;
+  uint32_t mx = 0;       // largest code of the thread's tile
+  int32_t flipped = -1;  // last flipped magnet (its spin bit still to toggle)
+  uint32_t* const tile = code + (tid << ts);
+  while (true) {
+    const bool mine = touched[tid] != 0u;
+    if (mine) {
+      touched[tid] = 0u;
+      // the chunks in a rotated order: lanes whose tiles start in the same
+      // bank read different chunks
+      uint32_t m = 0;
+      for (int u = 0; u < nc; ++u) {
+        const uint4 v = ((const uint4*)tile)[(u + lane) & (nc - 1)];
+        m = max(m, max(max(v.x, v.y), max(v.z, v.w)));
+      }
+      mx = m;
+    }
+    if (__ballot(mine)) {
+      const uint32_t m = wave_max_u32(mx);
+      uint32_t i = 0, cnt = 0;
+      if (m != 0u) {
+        const int wl = __ffsll((unsigned long long)__ballot(mx == m)) - 1;
+        i = (uint32_t)((wave * 64 + wl) << ts);
+        const uint32_t v = lane < per ? code[i + lane] : 0u;
+        cnt = (uint32_t)(__popcll(__ballot(mx >= m - kCodeNear)) + __popcll(__ballot(v >= m - kCodeNear)) - 1);
+        i += (uint32_t)(__ffsll((unsigned long long)__ballot(v == m)) - 1);
+      }
+      if (lane == 0) sh.best[wave] = make_uint4(m, i, cnt, 0u);
+    }
+    if (tid == 0) {
+      if (flipped >= 0) {
+        spin[flipped >> 5] ^= 1u << (flipped & 31);
+        flipped = -1;
+      }
+      if (deadline) sh.pause = (flips > flips0 && ((flips - flips0) & 15) == 0 && past(deadline)) ? 1 : 0;
+    }
+    __syncthreads();
+    const uint4 e = sh.best[lane & 15];
+    uint32_t M = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_max_u32(e.x));
+    if (M == 0u) break;
+    const uint32_t T = M - kCodeNear;
+    const int w = __ffsll((unsigned long long)__ballot(e.x == M)) - 1;
+    int32_t j = __builtin_amdgcn_readlane((int)e.y, w);
+    if (__popcll(__ballot(e.x >= T) & 0xffffull) > 1 || __builtin_amdgcn_readlane((int)e.z, w) > 1 ||
+        M < kCodeSure) {
+      // exact keys of the codes near the largest
+      double bk = 0.0;
+      uint32_t bp = 0x7fffffffu;
+      if (mx >= T)
+        for (int u = 0; u < per; ++u) {
+          const uint32_t v = tile[u];
+          if (v < T) continue;
+          const uint32_t i = (uint32_t)((tid << ts) + u);
+          double K;
+          if (v & kCodeExact) {
+            K = load_at(I->key, i * 8u);
+          } else {
+            const double2 h = load_at(I->h, i * 16u);
+            K = switching_key_far((v & kCodeDown) ? -1 : 1, h.x, h.y, load_at(I->hk, i * 8u), P.b,
+                                  P.c, P.ep, P.eq);
+            store_at(I->key, i * 8u, K);
+            tile[u] = K > 0.0 ? v | kCodeExact : 0u;
+            touched[tid] = 1u;
+          }
+          if (better(K, i, bk, bp)) {
+            bk = K;
+            bp = i;
+          }
+        }
+      // largest key, lowest index, over the wavefront and then the workgroup
+      const double wk = wave_max_f64(bk);
+      const uint32_t wi = ~wave_max_u32(bk == wk ? ~bp : 0u);
+      if (lane == 0) {
+        sh.rk[wave] = wk;
+        sh.ri[wave] = wi;
+      }
+      __syncthreads();
+      const int ql = lane & 15;
+      const double ek = ql < (NT >> 6) ? sh.rk[ql] : 0.0;
+      const uint32_t ei = ql < (NT >> 6) ? sh.ri[ql] : 0x7fffffffu;
+      const double rk = wave_max_f64(ek);
+      if (!(rk > 0.0)) continue;  // none of them can flip: the next codes
+      j = (int32_t)~wave_max_u32(ek == rk ? ~ei : 0u);
+      M = code[j];
+    }
+    if (deadline && sh.pause) {
+      status = 1;
+      break;
+    }
+    if (flips >= max_flips) {
+      status = -5;
+      break;
+    }
+    const bool down = (__builtin_amdgcn_readfirstlane((int)M) & kCodeDown) != 0u;
+    const double two = down ? 2.0 : -2.0;  // 2 s_new
+    const int64_t row = (int64_t)j * D;
+    const ASI_GLOBAL int32_t* const rc = I->rcol + row;
+    const ASI_GLOBAL double* const ra = I->rA + row;
+    const ASI_GLOBAL double* const rb = I->rBr + row;
+    for (int k = tid; k < D; k += NT) {
+      // the slot's column and couplings together (a padding slot holds -1 and
+      // zeros), then the neighbour's state: two round trips
+      const int32_t i0 = load_at(rc, (uint32_t)k * 4u);
+      const double ca = load_at(ra, (uint32_t)k * 8u);
+      const double cb = load_at(rb, (uint32_t)k * 8u);
+      const uint32_t i = (uint32_t)max(i0, 0);
+      const double2 hi = load_at(I->h, i * 16u);
+      const double hki = load_at(I->hk, i * 8u);
+      const double2 di = (mode == kFieldCarry) ? load_at(I->hd, i * 16u) : make_double2(0.0, 0.0);
+      const bool neg = (spin[i >> 5] >> (i & 31u)) & 1u;
+      const double da = two * ca, db = two * cb;
+      const double hp = hi.x + da, hq = hi.y + db;
+      const uint32_t v = key_code(neg, hp, hq, hki, P);
+      if (i0 >= 0) {
+        code[i] = v;
+        touched[i >> ts] = 1u;
+        store_at(I->h, i * 16u, make_double2(hp, hq));
+        if (mode == kFieldCarry)
+          store_at(I->hd, i * 16u, make_double2(di.x + da, di.y + db));
+        else if (mode == kFieldDirty)
+          store_at(I->dirty, i, (uint8_t)1);
+      }
+    }
+    if (tid == 0) {
+      code[j] = 0u;
+      touched[j >> ts] = 1u;
+      flipped = j;
+      store_at(I->s, (uint32_t)j, down ? (int8_t)1 : (int8_t)-1);
+      if (logpos < I->log_cap) {
+        I->log_t[logpos] = (int32_t)t;
+        I->log_j[logpos] = j;
+      }
+      hash = (hash ^ (((uint64_t)(uint32_t)t << 32) | (uint64_t)(uint32_t)j)) * 0x100000001b3ull;
+    }
+    ++logpos;
+    ++flips;
+    __syncthreads();
+  }
+  return status;
+}
+
 // Per-64-row maxima of the stored keys -- the lowest level of the relax
 // tree -- rebuilt by the whole workgroup, four 64-row groups per wavefront
 // at a time (their loads issued together).
@@ -2091,34 +2432,52 @@ __device__ __forceinline__ void rebuild_t1(const InstDev* __restrict__ I) {
 }
 
 // Relax one instance at step t (Sec. II.H) and advance its run cursor.
-// Steps that start with at least spec_min flippable magnets (and a degree
-// that leaves room for batches) take the speculative path; the others the
-// max tree; a speculative step whose batches stay small continues on the
-// tree; a paused step resumes on the path it was on.  Both flip exactly the
-// magnets, in exactly the order, of the one-at-a-time relax.
-// kSpec false: the launch holds no instance that may speculate (every degree
-// above kSpecMaxD, or a workgroup below 1024 threads), so the kernel carries
-// the max tree alone and its registers are allocated for that path.
-template <bool kSpec>
+// kPathLds: one flip at a time, the keys in LDS.  kPathSpec: steps that start
+// with at least spec_min flippable magnets (and a degree that leaves room for
+// batches) take the speculative path; the others the max tree; a speculative
+// step whose batches stay small continues on the tree; a paused step resumes
+// on the path it was on.  kPathTree: the max tree alone.  All flip exactly the
+// magnets, in exactly the order, of the one-at-a-time relax.  Each path is a
+// kernel of its own, so that its registers are allocated for that path.
+template <int kPath>
+struct RelaxState {
+  RelaxShared tree;
+  SpecShared spec;
+};
+template <>
+struct RelaxState<kPathTree> {
+  RelaxShared tree;
+};
+template <>
+struct RelaxState<kPathLds> {
+  FlipShared flip;
+};
+
+template <int kPath>
 __device__ __forceinline__ int relax_step(const InstDev* __restrict__ I, RunDev* __restrict__ R, int64_t t,
-                          unsigned char* lds_raw, RelaxShared& sh, SpecShared& ssh,
-                          uint64_t deadline) {
+                          unsigned char* lds_raw, RelaxState<kPath>& sh, uint64_t deadline) {
   const int64_t ncand = __hip_atomic_load(I->ccount, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const int64_t acc0 = R->step_acc;  // flips of step t before a pause
   int64_t flips = acc0;
   int64_t logpos = R->flips;
   uint64_t hash = R->hash;
-  bool spec = kSpec && blockDim.x == 1024 &&
-              (R->paused ? R->spec != 0 : (I->D <= kSpecMaxD && ncand >= I->spec_min));
-  int status = 2;
+  bool spec = false;
+  int status;
   if ((int64_t)(uint32_t)ncand > I->ccap) {
     status = kPoolOverflow;  // cannot happen while every pass starts from an empty pool
+  } else if constexpr (kPath == kPathLds) {
+    status = relax_lds(I, t, lds_raw, sh.flip, ncand, flips, logpos, hash, deadline);
+  } else if constexpr (kPath == kPathTree) {
+    status = relax_tree<true>(I, t, lds_raw, sh.tree, flips, logpos, hash, deadline);
   } else {
-    if (kSpec && spec) status = relax_spec(I, t, lds_raw, ssh, ncand, flips, logpos, hash, deadline);
+    spec = blockDim.x == 1024 &&
+           (R->paused ? R->spec != 0 : (I->D <= kSpecMaxD && ncand >= I->spec_min));
+    status = 2;
+    if (spec) status = relax_spec(I, t, lds_raw, sh.spec, ncand, flips, logpos, hash, deadline);
     if (status == 2) {
-      if (kSpec && spec) rebuild_t1(I);  // the keys have moved since the field phase
+      if (spec) rebuild_t1(I);  // the keys have moved since the field phase
       spec = false;
-      status = relax_tree<!kSpec>(I, t, lds_raw, sh, flips, logpos, hash, deadline);
+      status = relax_tree<false>(I, t, lds_raw, sh.tree, flips, logpos, hash, deadline);
     }
   }
   __syncthreads();
@@ -2146,17 +2505,18 @@ __device__ __forceinline__ int relax_step(const InstDev* __restrict__ I, RunDev*
   return status;
 }
 
-template <bool kSpec>
+template <int kPath>
 __global__ __launch_bounds__(64 * kMaxRelaxWaves) void k_relax(const InstDev* __restrict__ insts,
                                                               RunDev* __restrict__ runs) {
   RunDev* R = runs + blockIdx.x;
   // a relax paused at a burst deadline finishes its step here, its
   // structures rebuilt by the preceding field launch
   if (!R->active && !R->paused) return;
+  const InstDev* I = insts + blockIdx.x;
+  if ((I->lds_keys != 0) != (kPath == kPathLds)) return;  // relaxed by another launch
   extern __shared__ unsigned char lds_raw[];
-  __shared__ RelaxShared sh;
-  __shared__ SpecShared ssh;
-  relax_step<kSpec>(insts + blockIdx.x, R, R->t, lds_raw, sh, ssh, 0);
+  __shared__ RelaxState<kPath> sh;
+  relax_step<kPath>(I, R, R->t, lds_raw, sh, 0);
 }
 
 // One workgroup per instance runs whole field steps -- its own field phase,
@@ -2168,6 +2528,7 @@ __global__ __launch_bounds__(64 * kMaxRelaxWaves) void k_relax(const InstDev* __
 // step it stopped in first, its relax structures rebuilt (by the preceding
 // field launch when first_ready); the flips it makes, and their order, are
 // those of an uninterrupted relax.
+template <int kPath>
 __global__ __launch_bounds__(64 * kMaxRelaxWaves) void k_fused(const InstDev* __restrict__ insts,
                                                               RunDev* __restrict__ runs,
                                                               int64_t max_steps,
@@ -2177,9 +2538,9 @@ __global__ __launch_bounds__(64 * kMaxRelaxWaves) void k_fused(const InstDev* __
   const bool paused = R->paused != 0;
   if (!R->active && !paused) return;
   const InstDev* I = insts + blockIdx.x;
+  if ((I->lds_keys != 0) != (kPath == kPathLds)) return;  // run by another launch
   extern __shared__ unsigned char lds_raw[];
-  __shared__ RelaxShared sh;
-  __shared__ SpecShared ssh;
+  __shared__ RelaxState<kPath> sh;
   __shared__ int go;
   const int wave = threadIdx.x >> 6, NW = blockDim.x >> 6;
   const uint64_t t_start = wall_clock64();
@@ -2199,7 +2560,7 @@ __global__ __launch_bounds__(64 * kMaxRelaxWaves) void k_fused(const InstDev* __
       __syncthreads();
     }
     ready = false;
-    if (relax_step<true>(I, R, t, lds_raw, sh, ssh, deadline) != 0) break;
+    if (relax_step<kPath>(I, R, t, lds_raw, sh, deadline) != 0) break;
     if (threadIdx.x == 0) go = (R->active && !past(deadline)) ? 1 : 0;
     __syncthreads();
     if (!go) break;
@@ -2760,22 +3121,28 @@ void launch_field_hd(const InstDev* inst, RunDev* run, int64_t n, int32_t rows, 
 }
 
 void launch_relax(const InstDev* insts, RunDev* runs, int32_t count, int32_t waves,
-                  size_t lds_bytes, bool tree_only, hipStream_t st) {
+                  size_t lds_bytes, RelaxPath path, hipStream_t st) {
   if (count <= 0) return;
-  if (tree_only)
-    hipLaunchKernelGGL(k_relax<false>, dim3((unsigned)count), dim3(64 * waves), lds_bytes, st,
-                       insts, runs);
+  const dim3 g((unsigned)count), b((unsigned)(64 * waves));
+  if (path == kPathLds)
+    hipLaunchKernelGGL(k_relax<kPathLds>, g, b, lds_bytes, st, insts, runs);
+  else if (path == kPathTree)
+    hipLaunchKernelGGL(k_relax<kPathTree>, g, b, lds_bytes, st, insts, runs);
   else
-    hipLaunchKernelGGL(k_relax<true>, dim3((unsigned)count), dim3(64 * waves), lds_bytes, st,
-                       insts, runs);
+    hipLaunchKernelGGL(k_relax<kPathSpec>, g, b, lds_bytes, st, insts, runs);
 }
 
 void launch_fused(const InstDev* insts, RunDev* runs, int32_t count, int32_t waves,
-                  size_t lds_bytes, int64_t max_steps, int64_t budget_ticks,
+                  size_t lds_bytes, RelaxPath path, int64_t max_steps, int64_t budget_ticks,
                   int32_t first_ready, hipStream_t st) {
   if (count <= 0) return;
-  hipLaunchKernelGGL(k_fused, dim3((unsigned)count), dim3(64 * waves), lds_bytes, st, insts, runs,
-                     max_steps, budget_ticks, first_ready);
+  const dim3 g((unsigned)count), b((unsigned)(64 * waves));
+  if (path == kPathLds)
+    hipLaunchKernelGGL(k_fused<kPathLds>, g, b, lds_bytes, st, insts, runs, max_steps,
+                       budget_ticks, first_ready);
+  else
+    hipLaunchKernelGGL(k_fused<kPathSpec>, g, b, lds_bytes, st, insts, runs, max_steps,
+                       budget_ticks, first_ready);
 }
 
 void launch_set_run(RunDev* run, int32_t* ccount, int64_t t, int64_t t_end, int32_t active,
@@ -2796,17 +3163,22 @@ size_t relax_lds_bytes(int64_t n, int32_t l1_shift) {
   return a > b ? a : b;
 }
 
+size_t relax_keys_lds_bytes(int64_t n, int32_t waves) { return flip_lds_bytes(n, 64 * waves); }
+
 hipError_t configure_kernels() {
   // the relax kernels take more than 64 KB of dynamic LDS
-  const int bytes = (int)relax_lds_bytes((int64_t)kMaxL1Tiles << 6, 6);
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_relax<true>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_relax<false>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_fused),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  const int tree = (int)relax_lds_bytes((int64_t)kMaxL1Tiles << 6, 6);
+  const int keys = (int)flip_lds_bytes(kLdsMaxN, 64 * kMaxRelaxWaves);
+  const std::pair<const void*, int> k[] = {
+      {reinterpret_cast<const void*>(&k_relax<kPathTree>), tree},
+      {reinterpret_cast<const void*>(&k_relax<kPathSpec>), tree},
+      {reinterpret_cast<const void*>(&k_relax<kPathLds>), keys},
+      {reinterpret_cast<const void*>(&k_fused<kPathSpec>), tree},
+      {reinterpret_cast<const void*>(&k_fused<kPathLds>), keys}};
+  hipError_t e = hipSuccess;
+  for (const auto& f : k)
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute(f.first, hipFuncAttributeMaxDynamicSharedMemorySize, f.second);
   return e;
 }
 

@@ -104,6 +104,7 @@ struct asi_sim {
   int32_t D = 0, l1s = 6, relax_waves = 1;
   int32_t field_rows = 0;       // rows per workgroup of the high-degree pass (0: by size)
   size_t lds = 0;
+  RelaxPath path = kPathTree;
   InstDev hI{};
   InstDev* dI = nullptr;
   RunDev* dR = nullptr;
@@ -185,8 +186,7 @@ void relax_pass(asi_sim* s) {
     tp.kind = 1;
     (void)hipEventRecord(tp.a, s->stream);
   }
-  launch_relax(s->dI, s->dR, 1, s->relax_waves, s->lds, !relax_may_speculate(s->D, s->relax_waves),
-               s->stream);
+  launch_relax(s->dI, s->dR, 1, s->relax_waves, s->lds, s->path, s->stream);
   if (s->timing) {
     (void)hipEventRecord(tp.b, s->stream);
     s->timers.push_back(tp);
@@ -276,6 +276,14 @@ size_t footprint_estimate(int64_t n, int64_t D, int64_t K, int64_t log_cap) {
   if (D >= kHdMinD && nsl < kHdSplitSlices) b += (size_t)n * (size_t)((D + 63) / 64) * 16;
   b += 1 << 16;
   return b;
+}
+
+// Relax path and dynamic LDS of the handle's current shapes.
+void set_relax_path(asi_sim* s) {
+  const bool in_lds = relax_keys_in_lds(s->n, s->D, s->relax_waves, s->hI.spec_min);
+  s->hI.lds_keys = in_lds ? 1 : 0;
+  s->path = in_lds ? kPathLds : relax_may_speculate(s->D, s->relax_waves) ? kPathSpec : kPathTree;
+  s->lds = in_lds ? relax_keys_lds_bytes(s->n, s->relax_waves) : relax_lds_bytes(s->n, s->l1s);
 }
 
 asi_status create_impl(const asi_params* p, const asi_device* dev, asi_sim* s) {
@@ -482,10 +490,18 @@ asi_status create_impl(const asi_params* p, const asi_device* dev, asi_sim* s) {
   if (!I.ver || !I.ccount) return fail(ASI_ENOMEM, "device allocation failed (candidate pool)");
   HIPCHK(hipMemsetAsync(I.ver, 0, 4 * n, s->stream), s);
   HIPCHK(hipMemsetAsync(I.ccount, 0, 4, s->stream), s);
-  I.spec_min = 32;
+  I.spec_min = kSpecMinDefault;
   if (const char* e = std::getenv("ASI_SPEC_MIN")) I.spec_min = std::atoll(e);
   I.spec_switch = 2.5;
   if (const char* e = std::getenv("ASI_SPEC_SWITCH")) I.spec_switch = std::atof(e);
+  // 16 wavefronts: the speculative relax spreads up to 2048 member and
+  // neighbour slots over 1024 lanes; touched tiles are rescanned in parallel
+  s->relax_waves = kMaxRelaxWaves;
+  if (const char* w = std::getenv("ASI_RELAX_WAVES")) {
+    int v = std::atoi(w);
+    if (v >= 1 && v <= kMaxRelaxWaves) s->relax_waves = v;
+  }
+  set_relax_path(s);
   s->dI = dalloc<InstDev>(s, 1);
   s->dR = dalloc<RunDev>(s, 1);
   s->nblocks = (n + kFieldBlock - 1) / kFieldBlock;
@@ -505,14 +521,6 @@ asi_status create_impl(const asi_params* p, const asi_device* dev, asi_sim* s) {
          s);
   HIPCHK(hipMemcpyAsync(s->dI, &s->hI, sizeof(InstDev), hipMemcpyHostToDevice, s->stream), s);
   launch_set_run(s->dR, I.ccount, -1, -1, 0, 1, -1, s->stream);
-  // 16 wavefronts: the speculative relax spreads up to 2048 member and
-  // neighbour slots over 1024 lanes; touched tiles are rescanned in parallel
-  s->relax_waves = kMaxRelaxWaves;
-  if (const char* w = std::getenv("ASI_RELAX_WAVES")) {
-    int v = std::atoi(w);
-    if (v >= 1 && v <= kMaxRelaxWaves) s->relax_waves = v;
-  }
-  s->lds = relax_lds_bytes(n, s->l1s);
   return sync_and_check(s);
 }
 
@@ -1041,7 +1049,7 @@ static asi_status apply_tuning(asi_sim* h, const asi_tuning* t) {
   h->l1s = t->l1_shift;
   h->hI.l1_shift = t->l1_shift;
   h->hI.spec_min = t->spec_min;
-  h->lds = relax_lds_bytes(h->n, t->l1_shift);
+  set_relax_path(h);
   return upload_desc(h);
 }
 
@@ -1473,8 +1481,13 @@ struct Table {
   int32_t* blk_row0 = nullptr;
   int64_t nblocks = 0;
   int32_t waves = 1;
-  size_t lds = 0;
-  bool tree_only = false;  // no instance of the table may speculate
+  // Two groups of instances, relaxed side by side by kernels of their own:
+  // those on kPathLds and the others (kPathTree when none may speculate).
+  size_t lds_keys = 0, lds_other = 0;
+  bool any_keys = false, any_other = false;
+  RelaxPath other = kPathTree;
+  hipStream_t side = nullptr;  // the first group's launches, when there are both
+  hipEvent_t fork = nullptr, join = nullptr;
   hipGraphExec_t exec = nullptr;
   hipGraph_t graph = nullptr;
 
@@ -1484,15 +1497,31 @@ struct Table {
     exec = nullptr;
     graph = nullptr;
   }
+  // Stream and events of the side-by-side launches; false on a HIP error.
+  bool open_side() {
+    return (side || hipStreamCreateWithFlags(&side, hipStreamNonBlocking) == hipSuccess) &&
+           (fork || hipEventCreateWithFlags(&fork, hipEventDisableTiming) == hipSuccess) &&
+           (join || hipEventCreateWithFlags(&join, hipEventDisableTiming) == hipSuccess);
+  }
+  void close_side() {
+    if (side) {
+      (void)hipStreamSynchronize(side);
+      (void)hipStreamDestroy(side);
+    }
+    if (fork) (void)hipEventDestroy(fork);
+    if (join) (void)hipEventDestroy(join);
+    side = nullptr;
+    fork = join = nullptr;
+  }
   ~Table() {
     drop_graph();
+    close_side();
     mem.release_all();
   }
 };
 
 // (Re)build the launch tables for the given instance descriptors.
-asi_status table_build(Table& T, const std::vector<InstDev>& insts,
-                       const std::vector<int32_t>& waves, const std::vector<size_t>& lds,
+asi_status table_build(Table& T, std::vector<InstDev>& insts, const std::vector<int32_t>& waves,
                        hipStream_t st) {
   T.drop_graph();
   T.mem.st = st;
@@ -1500,7 +1529,6 @@ asi_status table_build(Table& T, const std::vector<InstDev>& insts,
   T.count = (int32_t)insts.size();
   std::vector<int32_t> bi, br;
   T.waves = 1;
-  T.lds = 0;
   for (int32_t k = 0; k < T.count; ++k) {
     const int64_t nb = (insts[k].n + kFieldBlock - 1) / kFieldBlock;
     for (int64_t b = 0; b < nb; ++b) {
@@ -1508,15 +1536,30 @@ asi_status table_build(Table& T, const std::vector<InstDev>& insts,
       br.push_back((int32_t)(b * kFieldBlock));
     }
     T.waves = std::max(T.waves, waves[k]);
-    T.lds = std::max(T.lds, lds[k]);
   }
   if (const char* w = std::getenv("ASI_BATCH_RELAX_WAVES")) {
     int v = std::atoi(w);
     if (v >= 1 && v <= kMaxRelaxWaves) T.waves = v;
   }
-  T.tree_only = true;
-  for (int32_t k = 0; k < T.count; ++k)
-    if (insts[k].n > 0 && relax_may_speculate(insts[k].D, T.waves)) T.tree_only = false;
+  T.lds_keys = T.lds_other = 0;
+  T.any_keys = T.any_other = false;
+  T.other = kPathTree;
+  for (int32_t k = 0; k < T.count; ++k) {
+    InstDev& I = insts[k];
+    if (I.n <= 0) continue;
+    // the path depends on the launch's workgroup size
+    I.lds_keys = relax_keys_in_lds(I.n, I.D, T.waves, I.spec_min) ? 1 : 0;
+    if (I.lds_keys) {
+      T.any_keys = true;
+      T.lds_keys = std::max(T.lds_keys, relax_keys_lds_bytes(I.n, T.waves));
+    } else {
+      T.any_other = true;
+      T.lds_other = std::max(T.lds_other, relax_lds_bytes(I.n, I.l1_shift));
+      if (relax_may_speculate(I.D, T.waves)) T.other = kPathSpec;
+    }
+  }
+  if (T.any_keys && T.any_other && !T.open_side())
+    return fail(ASI_EDEVICE, "stream creation failed (batch)");
   T.nblocks = (int64_t)bi.size();
   T.dI = static_cast<InstDev*>(T.mem.alloc(sizeof(InstDev) * std::max(1, T.count)));
   T.dR = static_cast<RunDev*>(T.mem.alloc(sizeof(RunDev) * std::max(1, T.count)));
@@ -1538,9 +1581,38 @@ asi_status table_build(Table& T, const std::vector<InstDev>& insts,
   return ASI_OK;
 }
 
+// launch(path, dynamic LDS, stream) for each group of instances present; with
+// both, the groups run side by side between st's earlier and later work.
+template <class F>
+void table_groups(Table& T, hipStream_t st, F launch) {
+  const bool both = T.any_keys && T.any_other;
+  if (both) {
+    (void)hipEventRecord(T.fork, st);
+    (void)hipStreamWaitEvent(T.side, T.fork, 0);
+  }
+  if (T.any_keys) launch(kPathLds, T.lds_keys, both ? T.side : st);
+  if (T.any_other) launch(T.other, T.lds_other, st);
+  if (both) {
+    (void)hipEventRecord(T.join, T.side);
+    (void)hipStreamWaitEvent(st, T.join, 0);
+  }
+}
+
+void table_relax(Table& T, hipStream_t st) {
+  table_groups(T, st, [&](RelaxPath p, size_t lds, hipStream_t s) {
+    launch_relax(T.dI, T.dR, T.count, T.waves, lds, p, s);
+  });
+}
+
+void table_fused(Table& T, int64_t max_steps, int64_t ticks, hipStream_t st) {
+  table_groups(T, st, [&](RelaxPath p, size_t lds, hipStream_t s) {
+    launch_fused(T.dI, T.dR, T.count, T.waves, lds, p, max_steps, ticks, 1, s);
+  });
+}
+
 void table_step(Table& T, hipStream_t st) {
   launch_field(T.dI, T.dR, T.blk_inst, T.blk_row0, T.nblocks, st);
-  launch_relax(T.dI, T.dR, T.count, T.waves, T.lds, T.tree_only, st);
+  table_relax(T, st);
 }
 
 asi_status table_capture(Table& T, hipStream_t st) {
@@ -1568,7 +1640,6 @@ extern "C" asi_status asi_batch_run(asi_handle* hs, int32_t count, int32_t mode,
   std::vector<InstDev> insts(count);
   std::vector<RunDev> runs(count);
   std::vector<int32_t> waves(count);
-  std::vector<size_t> lds(count);
   int64_t max_steps = 0;
   for (int32_t k = 0; k < count; ++k) {
     asi_sim* h = hs[k];
@@ -1576,7 +1647,6 @@ extern "C" asi_status asi_batch_run(asi_handle* hs, int32_t count, int32_t mode,
     if (st != ASI_OK) return st;
     insts[k] = h->hI;
     waves[k] = h->relax_waves;
-    lds[k] = h->lds;
     RunDev& r = runs[k];
     r.t = h->cur_step + 1;
     r.t_end = h->K;
@@ -1591,7 +1661,7 @@ extern "C" asi_status asi_batch_run(asi_handle* hs, int32_t count, int32_t mode,
   {
     Table T;
     T.mem.dev = hs[0]->mem.dev;
-    res = table_build(T, insts, waves, lds, st);
+    res = table_build(T, insts, waves, st);
     if (res == ASI_OK) {
       hipError_t e = hipMemcpyAsync(T.dR, runs.data(), sizeof(RunDev) * count,
                                     hipMemcpyHostToDevice, st);
@@ -1600,7 +1670,7 @@ extern "C" asi_status asi_batch_run(asi_handle* hs, int32_t count, int32_t mode,
     if (res == ASI_OK && max_steps > 0) {
       if (mode == 2) {
         launch_field(T.dI, T.dR, T.blk_inst, T.blk_row0, T.nblocks, st);
-        launch_fused(T.dI, T.dR, T.count, T.waves, T.lds, max_steps, 0, 1, st);
+        table_fused(T, max_steps, 0, st);
       } else {
         if (mode == 1) res = table_capture(T, st);
         for (int64_t s = 0; res == ASI_OK && s < max_steps; ++s) {
@@ -1764,7 +1834,6 @@ constexpr double kQuietBurstScale = 8.0;
 asi_status server_rebuild(asi_server* S) {
   std::vector<InstDev> insts(S->max_slots);
   std::vector<int32_t> waves(S->max_slots, 1);
-  std::vector<size_t> lds(S->max_slots, 0);
   for (int32_t k = 0; k < S->max_slots; ++k) {
     if (S->slots[k] < 0) {
       insts[k] = InstDev{};
@@ -1774,9 +1843,8 @@ asi_status server_rebuild(asi_server* S) {
     Job& J = *S->jobs[S->slots[k]];
     insts[k] = J.h->hI;
     waves[k] = J.h->relax_waves;
-    lds[k] = J.h->lds;
   }
-  asi_status st = table_build(S->T, insts, waves, lds, S->stream);
+  asi_status st = table_build(S->T, insts, waves, S->stream);
   if (st != ASI_OK) return st;
   HIPCHK(hipMemcpyAsync(S->T.dR, S->runs.data(), sizeof(RunDev) * S->max_slots,
                         hipMemcpyHostToDevice, S->stream),
@@ -1979,11 +2047,9 @@ asi_status asi_server_step(asi_server_t S, double budget_ms, int32_t* active_out
     const int64_t ticks = std::max<int64_t>(1, (int64_t)(budget_ms * 1e-3 * (double)S->clock_hz));
     launch_field(S->T.dI, S->T.dR, S->T.blk_inst, S->T.blk_row0, S->T.nblocks, S->stream);
     if (quiet)
-      launch_relax(S->T.dI, S->T.dR, S->T.count, S->T.waves, S->T.lds, S->T.tree_only,
-                   S->stream);
+      table_relax(S->T, S->stream);
     else
-      launch_fused(S->T.dI, S->T.dR, S->T.count, S->T.waves, S->T.lds, tail ? 1 : INT64_MAX,
-                   ticks, 1, S->stream);
+      table_fused(S->T, tail ? 1 : INT64_MAX, ticks, S->stream);
     HIPCHK(hipMemcpyAsync(S->rb, S->T.dR, sizeof(RunDev) * S->max_slots, hipMemcpyDeviceToHost,
                           S->stream),
            (asi_sim*)nullptr);
@@ -2013,10 +2079,9 @@ asi_status asi_server_step(asi_server_t S, double budget_ms, int32_t* active_out
       const int64_t ticks = std::max<int64_t>(1, (int64_t)(left * (double)S->clock_hz));
       launch_field(S->T.dI, S->T.dR, S->T.blk_inst, S->T.blk_row0, S->T.nblocks, S->stream);
       if (quiet)
-        launch_relax(S->T.dI, S->T.dR, S->T.count, S->T.waves, S->T.lds, S->T.tree_only,
-                   S->stream);
+        table_relax(S->T, S->stream);
       else
-        launch_fused(S->T.dI, S->T.dR, S->T.count, S->T.waves, S->T.lds, 1, ticks, 1, S->stream);
+        table_fused(S->T, 1, ticks, S->stream);
       HIPCHK(hipMemcpyAsync(S->rb, S->T.dR, sizeof(RunDev) * S->max_slots,
                             hipMemcpyDeviceToHost, S->stream),
              (asi_sim*)nullptr);
@@ -2203,6 +2268,7 @@ asi_status asi_server_destroy(asi_server_t S) {
     if (kv.second->h) asi_destroy(kv.second->h);
   S->jobs.clear();
   S->T.drop_graph();
+  S->T.close_side();
   S->T.mem.release_all();
   if (S->rb) (void)hipHostFree(S->rb);
   (void)hipStreamDestroy(S->cstream);
