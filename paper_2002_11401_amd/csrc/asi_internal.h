@@ -49,6 +49,7 @@ enum RelaxPath : int32_t {
   kPathTree = 0,  // max tree
   kPathSpec = 1,  // speculative batches or the max tree, by step
   kPathLds = 2,   // one flip at a time, every key in LDS
+  kPathLdsSpec = 3,  // speculative batches or the latter, by step
 };
 
 // How the dipolar sum of a row is obtained at the start of a field step.
@@ -74,11 +75,11 @@ struct InstDev {
   // The same rows row-major for the relax, which walks one row at a time
   // (a wavefront reads consecutive slots): slot k of row i at i * D + k.
   const ASI_GLOBAL int32_t* rcol;    // neighbour index j, -1 pads
-  const ASI_GLOBAL double* rA;       // A_ij
-  const ASI_GLOBAL double* rBr;      // mhatperp_j. c_ji  (field at neighbour j from row i)
+  const ASI_GLOBAL double2* rAB;     // (A_ij, mhatperp_j. c_ji: field at neighbour j from row i)
   const ASI_GLOBAL double* mx;       // [n] easy axis mhat_i = (mx, my)
   const ASI_GLOBAL double* my;
   const ASI_GLOBAL double* hk;       // [n] coercive field h_k^(i)
+  const ASI_GLOBAL double* ghk;      // [n] 1 / (b h_k^(i)), for n <= kLdsMaxN (else null)
   double b, c;            // astroid width parameters
   double e_par, e_perp;   // astroid exponents 2/gamma and 2/beta
   double sigma;           // thermal std
@@ -108,7 +109,7 @@ struct InstDev {
   // chunks: [nch][n] (easy, hard); null and nch == 0 when not allocated
   ASI_GLOBAL double2* part;
   int32_t nch;
-  int32_t lds_keys;       // relaxed on kPathLds (see relax_keys_in_lds)
+  int32_t lds_keys;       // on kPathLds or kPathLdsSpec (see relax_keys_in_lds)
   ASI_GLOBAL int32_t* log_t;         // flip log
   ASI_GLOBAL int32_t* log_j;
   int64_t log_cap;
@@ -123,7 +124,8 @@ struct InstDev {
   ASI_GLOBAL int32_t* ccount;        // entries in buffer 0 (field phase appends)
   int64_t ccap;
   int64_t spec_min;       // flippable magnets at step start to go speculative
-  double spec_switch;     // mean batch below which a speculative step goes on the tree
+  double spec_switch;     // mean batch below which a speculative step goes on one flip at a
+                          // time (0: the path's own)
 };
 
 // Per-instance run cursor, device-resident so repeated launches (and
@@ -203,6 +205,8 @@ hipError_t static_scratch_address(unsigned char** out);
 // elapsed device-clock ticks, out[1 + lane] = each lane's last index.
 void launch_chase(const int32_t* chain, const int32_t* starts, int32_t lanes, int64_t hops,
                   unsigned long long* out, hipStream_t st);
+// g[i] = 1 / (b hk[i]) for the approximated keys of kPathLds.
+void launch_inverse_hk(const double* hk, int64_t n, double b, double* g, hipStream_t st);
 void launch_neighbour_count(const double* x, const double* y, const int32_t* cellx,
                             const int32_t* celly, const int32_t* cell_start,
                             const int32_t* cell_members, int64_t n, int64_t gx, int64_t gy,
@@ -211,7 +215,7 @@ void launch_neighbour_fill(const double* x, const double* y, const double* mx, c
                            const int32_t* cellx, const int32_t* celly, const int32_t* cell_start,
                            const int32_t* cell_members, int64_t n, int64_t gx, int64_t gy,
                            double cut2, double alpha, int32_t D, int32_t* col, double* A,
-                           double* B, int32_t* rcol, double* rA, double* rBr, hipStream_t st);
+                           double* B, int32_t* rcol, double2* rAB, hipStream_t st);
 // Degree from which a single instance's full-field pass (every row
 // gathered) uses one workgroup per 64-row slice instead of one lane per row.
 constexpr int kHdMinD = 128;
@@ -236,18 +240,25 @@ void launch_field(const InstDev* insts, RunDev* runs, const int32_t* blk_inst,
 inline bool relax_may_speculate(int32_t D, int32_t waves) {
   return waves == kMaxRelaxWaves && D <= kSpecMaxD;
 }
-// Whether it is relaxed one flip at a time with every key in LDS: where they
-// fit (a thread owns at most 64 magnets), unless the caller asked for
-// speculation from a number of flippable magnets that it can reach.
-inline bool relax_keys_in_lds(int64_t n, int32_t D, int32_t waves, int64_t spec_min) {
-  return n <= kLdsMaxN && n <= (int64_t)64 * 64 * waves &&
-         (spec_min == kSpecMinDefault || spec_min > n || !relax_may_speculate(D, waves));
+// Whether its one-at-a-time relax holds every key in LDS: where they fit (a
+// thread owns at most 60 magnets, a row's byte offset has 32 bits) and the
+// parameters lie in the range of the approximated keys.
+inline bool relax_keys_in_lds(const InstDev& I, int32_t waves) {
+  return I.n <= kLdsMaxN && I.n <= (int64_t)60 * 64 * waves &&
+         I.n * I.D < ((int64_t)1 << 28) && I.e_par >= 0.25 && I.e_par <= 4.0 &&
+         I.e_perp >= 0.25 && I.e_perp <= 4.0 && I.b > 0x1p-60 && I.b < 0x1p60 &&
+         I.c > 0x1p-60 && (I.c < 0x1p60 || I.b / I.c == 0.0);
+}
+// The path of an instance, or of a table's instances of one kind.
+inline RelaxPath relax_path(bool keys_in_lds, bool may_speculate) {
+  return keys_in_lds ? (may_speculate ? kPathLdsSpec : kPathLds)
+                     : (may_speculate ? kPathSpec : kPathTree);
 }
 // One workgroup per instance: relax the current step of the instances on
-// `path` (kPathTree only where no other instance of the table may speculate).
+// `path` (kPathTree or kPathLds only where none of its kind may speculate).
 void launch_relax(const InstDev* insts, RunDev* runs, int32_t count, int32_t waves,
                   size_t lds_bytes, RelaxPath path, hipStream_t st);
-// One workgroup per instance, of those on kPathLds or of the others: up to
+// One workgroup per instance, of those with keys in LDS or of the others: up to
 // max_steps whole steps (field phase and relax) per instance.  With
 // budget_ticks > 0 a workgroup stops once that many ticks of the
 // device's constant-rate clock have passed: between steps, or inside a relax
@@ -265,9 +276,9 @@ void launch_set_run(RunDev* run, int32_t* ccount, int64_t t, int64_t t_end, int3
 // (an internal error: the host reports ASI_EDEVICE).
 constexpr int32_t kPoolOverflow = -3;
 // Dynamic LDS of the relax and fused kernels for an instance of n magnets: of
-// the tree and speculative paths, and of kPathLds.
+// the tree and speculative paths, and of those with keys in LDS.
 size_t relax_lds_bytes(int64_t n, int32_t l1_shift);
-size_t relax_keys_lds_bytes(int64_t n, int32_t waves);
+size_t relax_keys_lds_bytes(int64_t n, int32_t waves, bool spec);
 int32_t relax_l1_shift(int64_t n);
 // Raise the dynamic-LDS limit of the relax kernels (call once per process).
 hipError_t configure_kernels();

@@ -113,78 +113,78 @@ __device__ inline double switching_key(int s, double hp, double hq, double hk, d
 
 // The exact key for the rare lanes of a relax that need it: out of line, so
 // that the FP64 powers' registers and constants stay out of the relax loop.
-__device__ __attribute__((noinline)) double switching_key_far(int s, double hp, double hq,
-                                                              double hk, double b, double c,
-                                                              double ep, double eq) {
-  return switching_key(s, hp, hq, hk, b, c, ep, eq);
+__device__ __attribute__((noinline)) double switching_key_far(const InstDev* __restrict__ I,
+                                                              bool neg, double hp, double hq,
+                                                              double hk) {
+  return switching_key(neg ? -1 : 1, hp, hq, hk, I->b, I->c, I->e_par, I->e_perp);
 }
 
-// Single-precision code of a key: the float bits of an approximation k of
-// Eq. 5's left-hand side (positive floats order like their bits) with the two
-// lowest bits replaced by flags; 0 when the magnet certainly cannot flip.
-// k is within kCodeRel of the FP64 key (of the left-hand side, where that is
-// at most 1):
+// 32-bit code of a key for the relax that holds its keys in LDS: an
+// approximation k of Eq. 5's left-hand side in the upper 24 bits (the float's
+// bits above those of just below 1, less the lowest three: ordered like k, up
+// to kCodeTop), two flags, and in the lowest 6 bits the magnet's place in its
+// thread's tile; 0 when the magnet certainly cannot flip.
+// The relative distance of k from the FP64 key (from the left-hand side, where
+// that is at most 1) is bounded so:
 //   - the normalised components are formed in FP64 and rounded once, 2^-24;
 //   - v_log_f32 and v_exp_f32 are within an ulp.  With exponents e in
-//     [1/4, 4] and k < 16, |e log2 x| <= 4 for the term that matters, so its
-//     error is below 4 * 2^-22 + 4 * (1.45 * 2^-24 + 2^-24) = 1.54e-6, the
-//     term's relative error below 1.54e-6 * ln 2 + 2^-23 and the sum's below
-//     1.3e-6 < 2^-19 (a small term errs less against the sum);
+//     [1/4, 4], x the normalised component, the exponent e log2 x of the term
+//     that matters is in error by at most |e log2 x| 2^-22 + 4 * 2.45 * 2^-24;
+//     the term, and the sum, by that times ln 2, and 2^-23: 1.3e-6 (below
+//     kCodeRel) for k < 16, where |e log2 x| < 4, 3.2e-6 for k < 2^16 (a small
+//     term errs less against the sum);
 //   - a component that underflows loses a term below (2^-126)^(1/4).
-// Measured over 3e9 random fields and parameters of those ranges: 6.9e-7 at
-// most.  Outside them (of the parameters: fast == false; of a lane: k or h_k)
-// the FP64 key itself is rounded.
+// Measured over 3e9 random fields and parameters: 7.0e-7 for k < 16, 2.1e-6
+// for k < 2^16.  Instances with parameters outside these ranges are relaxed on
+// other paths; a lane's k or h_k outside them (k_inverse_hk marks the latter by
+// NaN) gives kCodeUnknown, which the relax replaces by the exact key's code.
 constexpr float kCodeRel = 0x1p-19f;
-// Codes at least this far below a code belong to keys certainly below its
-// key: approximations whose ratio is below 1 - 2 kCodeRel, that is at most
-// 2 * 2^-19 * 2^24 = 64 units in the last place, and the flags and roundings.
-constexpr uint32_t kCodeNear = 76;
-// From here the key is certainly above 1 (kCodeRel is 16 units above 1).
-constexpr uint32_t kCodeSure = 0x3f800000u + 40u;
-constexpr uint32_t kCodeDown = 1u;   // flag: the spin is -1
-constexpr uint32_t kCodeExact = 2u;  // flag: the key array holds the FP64 key
+constexpr uint32_t kCodeBase = 0x3f800000u - 256u;
+constexpr float kCodeTop = 65000.0f;  // keys from here on share a code
+constexpr uint32_t kCodePlace = 63u;
+constexpr uint32_t kCodeDown = 64u;    // flag: the spin is -1
+constexpr uint32_t kCodeExact = 128u;  // flag: the key array holds the FP64 key
+__host__ __device__ constexpr uint32_t code_bits(uint32_t float_bits) {
+  return ((float_bits - kCodeBase) >> 3) << 8;
+}
+// Codes below code_floor(v) belong to keys certainly below v's: v less eleven
+// units (of 8 units in the last place of a float), and up to eight more with
+// v.  Two approximations in the order of their keys, or a ratio of 1 - 2 * the
+// bound above apart at most: 2 * 1.3e-6 * 2^24 = 44 units in the last place
+// for k < 16 (and two code roundings, 16), 108 for k < 2^16.
+__device__ inline uint32_t code_floor(uint32_t v) { return (v & ~255u) - (11u << 8) - (v >> 21); }
+// From here the key is certainly above 1 (kCodeRel is 16 units in the last
+// place above 1).
+constexpr uint32_t kCodeSure = code_bits(0x3f800000u + 40u);
+constexpr uint32_t kCodeUnknown = code_bits(0x477de800u) + 256u;  // above kCodeTop's
 
 struct KeyPar {
-  double b, c, ep, eq;   // Eq. 5 in FP64
-  double ib, ic;
-  float fep, feq;
-  bool fast;             // the approximation's error bound holds
+  double bc;     // b / c (0 for c = infinity: no hard-axis term)
+  float ep, eq;
 };
 
 __device__ inline KeyPar key_par(const InstDev* __restrict__ I) {
-  KeyPar P;
-  P.b = I->b;
-  P.c = I->c;
-  P.ep = I->e_par;
-  P.eq = I->e_perp;
-  P.ib = 1.0 / P.b;
-  P.ic = 1.0 / P.c;  // 0 for c = infinity: no hard-axis term
-  P.fep = (float)P.ep;
-  P.feq = (float)P.eq;
-  P.fast = P.ep >= 0.25 && P.ep <= 4.0 && P.eq >= 0.25 && P.eq <= 4.0 && P.b > 0x1p-60 &&
-           P.b < 0x1p60 && P.c > 0x1p-60 && (P.c < 0x1p60 || P.ic == 0.0);
-  return P;
+  return KeyPar{I->b / I->c, (float)I->e_par, (float)I->e_perp};
 }
 
-// Code of an FP64 key (keys past the range of a float share the largest
-// code), with the spin's flag.
+// Code of an FP64 key, without its place.
 __device__ inline uint32_t code_of_key(double key, bool neg) {
   if (!(key > 0.0)) return 0u;
-  return (__float_as_uint((float)fmin(key, 0x1p127)) & ~3u) | (neg ? kCodeDown : 0u);
+  const float k = (float)fmin(key, (double)kCodeTop);
+  return code_bits(__float_as_uint(k)) | (neg ? kCodeDown : 0u);
 }
 
-__device__ inline uint32_t key_code(bool neg, double hp, double hq, double hk, const KeyPar& P) {
-  const float fk = (float)hk;
-  const double r0 = (double)__builtin_amdgcn_rcpf(fk);
-  const double r = __builtin_fma(__builtin_fma(-hk, r0, 1.0), r0, r0);  // 1 / h_k
-  const float a = (float)(fabs(hp) * r * P.ib);
-  const float q = (float)(fabs(hq) * r * P.ic);
-  const float k = __builtin_amdgcn_exp2f(P.fep * __builtin_amdgcn_logf(a)) +
-                  __builtin_amdgcn_exp2f(P.feq * __builtin_amdgcn_logf(q));
-  const bool against = neg ? hp > 0.0 : hp < 0.0;
-  if (__builtin_expect(against && !(P.fast && k < 16.0f && fk > 0x1p-60f && fk < 0x1p60f), 0))
-    return code_of_key(switching_key_far(neg ? -1 : 1, hp, hq, hk, P.b, P.c, P.ep, P.eq), neg);
-  return against && k > 1.0f - kCodeRel ? (__float_as_uint(k) & ~3u) | (neg ? kCodeDown : 0u) : 0u;
+// Code of the key from the field, without its place; g = 1 / (b h_k).
+__device__ __forceinline__ uint32_t key_code(bool neg, double hp, double hq, double g,
+                                             const KeyPar& P) {
+  const float a = (float)(fabs(hp) * g);
+  const float q = (float)(fabs(hq) * g * P.bc);
+  const float k = __builtin_amdgcn_exp2f(P.ep * __builtin_amdgcn_logf(a)) +
+                  __builtin_amdgcn_exp2f(P.eq * __builtin_amdgcn_logf(q));
+  uint32_t v = k < kCodeTop ? code_bits(__float_as_uint(k)) : kCodeUnknown;  // NaN: unknown
+  v |= neg ? kCodeDown : 0u;
+  const bool can = ((neg ? hp : -hp) > 0.0) & !(k <= 1.0f - kCodeRel);
+  return can ? v : 0u;
 }
 
 // Eq. 3 for a unit source moment mhat_s at (sx, sy) seen at (fx, fy),
@@ -238,23 +238,26 @@ __device__ inline double wave_max_f64(double v) {
   return fmax(fmax(r0, r1), fmax(r2, r3));
 }
 
+// max(v, v moved by DPP): lanes without a source take 0.
+template <int CTRL, int ROWS = 0xF>
+__device__ inline uint32_t max_dpp_u32(uint32_t v) {
+  return max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false));
+}
+
 // Maximum of an unsigned value over each row of 16 lanes, in every lane.
 __device__ inline uint32_t row_max_u32(uint32_t v) {
-  v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, false));
-  v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, false));
-  v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xF, 0xF, false));
-  v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x140, 0xF, 0xF, false));
-  return v;
+  v = max_dpp_u32<0xB1>(v);     // quad_perm [1,0,3,2]
+  v = max_dpp_u32<0x4E>(v);     // quad_perm [2,3,0,1]
+  v = max_dpp_u32<0x141>(v);    // row_half_mirror
+  return max_dpp_u32<0x140>(v); // row_mirror
 }
 
 // Maximum over the 64 lanes, uniform.
 __device__ inline uint32_t wave_max_u32(uint32_t v) {
   v = row_max_u32(v);
-  const uint32_t r0 = (uint32_t)__builtin_amdgcn_readlane((int)v, 0);
-  const uint32_t r1 = (uint32_t)__builtin_amdgcn_readlane((int)v, 16);
-  const uint32_t r2 = (uint32_t)__builtin_amdgcn_readlane((int)v, 32);
-  const uint32_t r3 = (uint32_t)__builtin_amdgcn_readlane((int)v, 48);
-  return max(max(r0, r1), max(r2, r3));
+  v = max_dpp_u32<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
+  v = max_dpp_u32<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
 // Wave-wide argmax of (key, payload) where lane order is index order:
@@ -290,6 +293,16 @@ __global__ void k_draw_hk(double* __restrict__ hk, int64_t n, double mean, doubl
   const double h = mean + sd * z0;
   const double lo = 1e-12 * mean;
   hk[i] = h < lo ? lo : h;
+}
+
+// 1 / (b h_k) for key_code; NaN where h_k or the result is outside the range
+// in which its approximation holds.
+__global__ void k_inverse_hk(const double* __restrict__ hk, int64_t n, double b,
+                             double* __restrict__ g) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const double v = hk[i];
+  g[i] = v > 0x1p-60 && v < 0x1p60 ? 1.0 / (b * v) : __longlong_as_double(0x7ff8000000000000ll);
 }
 
 // Cells of side >= the cutoff, magnets sorted by cell (ascending index
@@ -336,7 +349,7 @@ __global__ void k_nb_fill(const double* __restrict__ x, const double* __restrict
                           int64_t n, int64_t gx, int64_t gy, double cut2, double alpha,
                           int32_t D, int32_t* __restrict__ col, double* __restrict__ A,
                           double* __restrict__ B, int32_t* __restrict__ rcol,
-                          double* __restrict__ rA, double* __restrict__ rBr) {
+                          double2* __restrict__ rAB) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const double xi = x[i], yi = y[i], mxi = mx[i], myi = my[i];
@@ -386,8 +399,7 @@ __global__ void k_nb_fill(const double* __restrict__ x, const double* __restrict
     B[sl] = b;
     const int64_t rs = i * D + k;
     rcol[rs] = j;
-    rA[rs] = a;
-    rBr[rs] = bt;
+    rAB[rs] = make_double2(a, bt);
     ++k;
   }
   for (; k < D; ++k) {
@@ -397,8 +409,7 @@ __global__ void k_nb_fill(const double* __restrict__ x, const double* __restrict
     B[sl] = 0.0;
     const int64_t rs = i * D + k;
     rcol[rs] = -1;
-    rA[rs] = 0.0;
-    rBr[rs] = 0.0;
+    rAB[rs] = make_double2(0.0, 0.0);
   }
 }
 
@@ -874,6 +885,25 @@ __global__ __launch_bounds__(256) void k_slice_max(const InstDev* __restrict__ i
   }
 }
 
+// Values that the whole workgroup shares but the compiler cannot know to be
+// the same in every lane (arguments of a function called out of line, values
+// read from LDS); a descriptor, which no kernel writes, also lies in constant
+// memory (scalar loads).
+#define ASI_LDS __attribute__((address_space(3)))
+#define ASI_CONST __attribute__((address_space(4)))
+
+__device__ __forceinline__ const InstDev* uniform(const InstDev* p) {
+  const uint64_t v = (uint64_t)p;
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+  return (const InstDev*)(const ASI_CONST InstDev*)((uint64_t)hi << 32 | lo);
+}
+__device__ __forceinline__ int64_t uniform(int64_t v) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)v >> 32));
+  return (int64_t)((uint64_t)hi << 32 | lo);
+}
+
 // ------------------------------------------------------------ relax
 struct RelaxLds {
   double* l1k;                // first level: maximum key of each tile
@@ -968,11 +998,16 @@ constexpr int kWin = 2048;        // hot window entries
 constexpr int kHash = 4096;       // conflict table slots
 constexpr int kMaxPairs = 2048;   // member + neighbour slots per batch
 constexpr int kMaxMembers = 64;
-// A step whose first kSwitchBatches batches commit fewer than spec_switch
-// (2.5 unless overridden) flips each on average -- an avalanche: every flip
+// A step whose first kSwitchBatches batches commit fewer than kSwitchFlips
+// (unless spec_switch is given) flips each on average -- an avalanche: every flip
 // makes a neighbour the next candidate -- continues on the max tree, which
 // costs about half a batch per flip on such steps.
 constexpr int kSwitchBatches = 16;
+// Where the one-at-a-time relax holds its keys in LDS, a batch costs about
+// nine of its flips: such a step goes over when four batches in a row commit
+// fewer than nine flips each on average.
+constexpr int kSwitchBatchesLds = 4;
+constexpr double kSwitchFlips = 2.5, kSwitchFlipsLds = 9.0;
 
 // Relax order of two magnets: larger key first, then lower index.
 __device__ inline bool better(double ka, uint32_t pa, double kb, uint32_t pb) {
@@ -1405,7 +1440,7 @@ __device__ inline uint32_t hash_slot(uint32_t i) { return (i * 2654435761u) >> (
 // logpos and hash are the running counters (hash significant in thread 0).
 // Returns 0, -5 (flip cap reached with a flippable magnet left),
 // 1 (deadline passed after at least one batch, flippable magnets left) or
-// 2 (after kSwitchBatches batches the mean batch is below spec_switch flips:
+// 2 (the mean batch is too small, see kSwitchBatches:
 // the flippable magnets crowd each other's neighbourhoods, and the step
 // goes on one flip at a time).
 __device__ __forceinline__ int relax_spec(const InstDev* __restrict__ I, int64_t t, unsigned char* lds,
@@ -1437,11 +1472,20 @@ __device__ __forceinline__ int relax_spec(const InstDev* __restrict__ I, int64_t
   __syncthreads();
   int status = 0;
   const int64_t flips0 = flips;
-  int nbatch = 0;
+  const bool keys_in_lds = I->lds_keys != 0;
+  const int nswitch = keys_in_lds ? kSwitchBatchesLds : kSwitchBatches;
+  const double sw = I->spec_switch > 0.0 ? I->spec_switch
+                                         : keys_in_lds ? kSwitchFlipsLds : kSwitchFlips;
+  int64_t flips1 = flips;
+  int nbatch = 0;  // batches since flips1
   while (true) {
-    if (nbatch >= kSwitchBatches && (double)(flips - flips0) < I->spec_switch * nbatch) {
+    if (nbatch >= nswitch && (double)(flips - flips1) < sw * nbatch) {
       status = 2;
       break;
+    }
+    if (keys_in_lds && nbatch == nswitch) {
+      flips1 = flips;
+      nbatch = 0;
     }
     if (tid < 64) {
       const int sf = count_safe_wave(S, sh);
@@ -1493,8 +1537,9 @@ __device__ __forceinline__ int relax_spec(const InstDev* __restrict__ I, int64_t
         } else {
           const int64_t sl = (int64_t)j * D + k;
           pr_i[u] = I->rcol[sl];
-          pr_a[u] = I->rA[sl];
-          pr_b[u] = I->rBr[sl];
+          const double2 ab = I->rAB[sl];
+          pr_a[u] = ab.x;
+          pr_b[u] = ab.y;
         }
       }
     }
@@ -1767,8 +1812,7 @@ __device__ __forceinline__ int relax_tree(const InstDev* __restrict__ I, int64_t
 
   const int32_t D = I->D;
   const int32_t* __restrict__ colp = I->rcol;
-  const double* __restrict__ Ap = I->rA;
-  const double* __restrict__ Brp = I->rBr;
+  const double2* __restrict__ ABp = I->rAB;
   const double* __restrict__ hkp = I->hk;
   int8_t* __restrict__ sp = I->s;
   double2* __restrict__ hp2 = I->h;
@@ -1955,8 +1999,8 @@ __device__ __forceinline__ int relax_tree(const InstDev* __restrict__ I, int64_t
       // and zeros), then every load of the neighbour's state before any
       // store, so that each costs one round trip
       const int32_t i = pre ? pf_c[h & 1] : colp[sl];
-      const double ca = pre ? pf_a[h & 1] : Ap[sl];
-      const double cb = pre ? pf_b[h & 1] : Brp[sl];
+      const double2 cab = pre ? make_double2(pf_a[h & 1], pf_b[h & 1]) : ABp[sl];
+      const double ca = cab.x, cb = cab.y;
       if (i >= 0) {
         const double2 hi = hp2[i];
         const double2 di = (mode == kFieldCarry) ? hd2[i] : make_double2(0.0, 0.0);
@@ -2055,8 +2099,9 @@ __device__ __forceinline__ int relax_tree(const InstDev* __restrict__ I, int64_t
           if (k < D) {
             const int64_t sl = pf_j * D + k;
             pf_c[h] = colp[sl];
-            pf_a[h] = Ap[sl];
-            pf_b[h] = Brp[sl];
+            const double2 ab = ABp[sl];
+            pf_a[h] = ab.x;
+            pf_b[h] = ab.y;
           }
         }
       }
@@ -2159,247 +2204,6 @@ __device__ __forceinline__ int relax_tree(const InstDev* __restrict__ I, int64_t
   return status;
 }
 
-// ------------------------------------------------------------ relax, keys in LDS
-// One-at-a-time relax for instances whose keys fit in LDS (kLdsMaxN magnets):
-// the code of every magnet, a spin bit per magnet, and per wavefront the best
-// code of the magnets its threads own.
-__host__ __device__ inline int flip_tile_shift(int64_t n, int threads) {
-  int sh = 2;
-  while (((int64_t)threads << sh) < n) ++sh;
-  return sh;
-}
-
-__host__ __device__ inline size_t flip_lds_bytes(int64_t n, int threads) {
-  const int sh = flip_tile_shift(n, threads);
-  const size_t tiles = (size_t)((n + (1LL << sh) - 1) >> sh);
-  return (tiles << sh) * 4 + align16((size_t)((n + 31) / 32) * 4) + (size_t)threads * 4;
-}
-
-struct FlipShared {
-  uint4 best[kMaxRelaxWaves];  // per wavefront: code, index, codes near it
-  double rk[kMaxRelaxWaves];   // resolving a near-tie: per wavefront exact key and index
-  uint32_t ri[kMaxRelaxWaves];
-  int pause;
-};
-
-// A global load at a 32-bit byte offset from a uniform base.
-template <class T>
-__device__ __forceinline__ T load_at(const ASI_GLOBAL T* base, uint32_t bytes) {
-  return *(const ASI_GLOBAL T*)((const ASI_GLOBAL char*)base + bytes);
-}
-template <class T>
-__device__ __forceinline__ void store_at(ASI_GLOBAL T* base, uint32_t bytes, T v) {
-  *(ASI_GLOBAL T*)((ASI_GLOBAL char*)base + bytes) = v;
-}
-
-// Relax at step t, one flip at a time.  Each thread owns a tile of
-// consecutive magnets and keeps its largest code in a register.  Per flip:
-//   - the wavefronts' best codes give the winner.  If no other code lies
-//     within kCodeNear of it, and it is surely above 1, it is the magnet the
-//     exact keys would pick; else the exact FP64 keys of the codes that near
-//     decide (keys of 0 are struck out, equal keys go to the lower index);
-//     an exact key is kept in the key array until the magnet's field changes;
-//   - the threads update the neighbours' fields and codes;  [barrier]
-//   - the owners of changed tiles rescan them in LDS and their wavefronts
-//     renew their best.  [barrier]
-// What bounds it: one dependent chain per flip -- the flipped magnet's row,
-// then its neighbours' fields (two round trips to memory), two barriers and
-// four LDS round trips.  Against the max tree it leaves out of that chain the
-// FP64 powers (~200 dependent instructions each; exact keys are evaluated for
-// 1-8 % of the flips), the rescans of tiles in memory and three of five
-// barriers: per flip 6.2 -> 2.1 us on a 5,100-magnet anneal at 632
-// neighbours, 5.6 -> 2.6 on a 20,200-magnet reversal at 632, 5.1 -> 2.2 on a
-// 29,040-magnet reversal at 60; with every key tied (no disorder) 5.1 -> 2.0.
-// Returns as relax_tree.
-__device__ __forceinline__ int relax_lds(const InstDev* __restrict__ I, int64_t t, unsigned char* lds_raw,
-                                         FlipShared& sh, int64_t ncand, int64_t& flips,
-                                         int64_t& logpos, uint64_t& hash, uint64_t deadline) {
-  if (ncand == 0) return 0;  // nothing can flip
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int NT = blockDim.x;
-  const int32_t n = (int32_t)I->n;
-  const int ts = flip_tile_shift(n, NT);
-  const int per = 1 << ts, nc = per >> 2;
-  const int32_t npad = ((n + per - 1) >> ts) << ts;
-  uint32_t* const code = (uint32_t*)lds_raw;
-  uint32_t* const spin = code + npad;  // bit per magnet: spin -1
-  // per thread: a code of its tile changed
-  uint32_t* const touched = (uint32_t*)((unsigned char*)spin + align16((size_t)((n + 31) / 32) * 4));
-
-  const int32_t D = I->D;
-  const int32_t mode = I->field_mode;
-  const KeyPar P = key_par(I);
-  const int64_t max_flips = I->max_flips;
-  const int64_t flips0 = flips;
-
-  for (int q = tid; q < npad / 4; q += NT) ((uint4*)code)[q] = make_uint4(0u, 0u, 0u, 0u);
-  // sign bits of 32 spins per word, from four 8-byte loads (the array's
-  // allocation is a multiple of 256 bytes)
-  for (int q = tid; q < (n + 31) / 32; q += NT) {
-    const ASI_GLOBAL uint64_t* s8 = (const ASI_GLOBAL uint64_t*)I->s + 4 * (int64_t)q;
-    uint64_t v[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = (8 * (4 * q + u) < n) ? s8[u] : 0ull;
-    uint32_t w = 0;
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      w |= (uint32_t)((((v[u] >> 7) & 0x0101010101010101ull) * 0x0102040810204080ull) >> 56) << (8 * u);
-    spin[q] = w;
-  }
-  touched[tid] = 0u;
-  if (tid < kMaxRelaxWaves) sh.best[tid] = make_uint4(0u, 0u, 0u, 0u);
-  if (tid == 0) sh.pause = 0;
-  __syncthreads();
-  // the field phase's list of flippable magnets, whose keys it also stored
-  for (int64_t q = tid; q < ncand; q += NT) {
-    const uint32_t pay = I->cpay[0][q];
-    const uint32_t i = pay & 0x7fffffffu;
-    code[i] = code_of_key(I->ckey[0][q], (pay >> 31) != 0u) | kCodeExact;
-    touched[i >> ts] = 1u;
-  }
-  __syncthreads();
-
-  int status = 0;
-  uint32_t mx = 0;       // largest code of the thread's tile
-  int32_t flipped = -1;  // last flipped magnet (its spin bit still to toggle)
-  uint32_t* const tile = code + (tid << ts);
-  while (true) {
-    const bool mine = touched[tid] != 0u;
-    if (mine) {
-      touched[tid] = 0u;
-      // the chunks in a rotated order: lanes whose tiles start in the same
-      // bank read different chunks
-      uint32_t m = 0;
-      for (int u = 0; u < nc; ++u) {
-        const uint4 v = ((const uint4*)tile)[(u + lane) & (nc - 1)];
-        m = max(m, max(max(v.x, v.y), max(v.z, v.w)));
-      }
-      mx = m;
-    }
-    if (__ballot(mine)) {
-      const uint32_t m = wave_max_u32(mx);
-      uint32_t i = 0, cnt = 0;
-      if (m != 0u) {
-        const int wl = __ffsll((unsigned long long)__ballot(mx == m)) - 1;
-        i = (uint32_t)((wave * 64 + wl) << ts);
-        const uint32_t v = lane < per ? code[i + lane] : 0u;
-        cnt = (uint32_t)(__popcll(__ballot(mx >= m - kCodeNear)) + __popcll(__ballot(v >= m - kCodeNear)) - 1);
-        i += (uint32_t)(__ffsll((unsigned long long)__ballot(v == m)) - 1);
-      }
-      if (lane == 0) sh.best[wave] = make_uint4(m, i, cnt, 0u);
-    }
-    if (tid == 0) {
-      if (flipped >= 0) {
-        spin[flipped >> 5] ^= 1u << (flipped & 31);
-        flipped = -1;
-      }
-      if (deadline) sh.pause = (flips > flips0 && ((flips - flips0) & 15) == 0 && past(deadline)) ? 1 : 0;
-    }
-    __syncthreads();
-    const uint4 e = sh.best[lane & 15];
-    uint32_t M = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_max_u32(e.x));
-    if (M == 0u) break;
-    const uint32_t T = M - kCodeNear;
-    const int w = __ffsll((unsigned long long)__ballot(e.x == M)) - 1;
-    int32_t j = __builtin_amdgcn_readlane((int)e.y, w);
-    if (__popcll(__ballot(e.x >= T) & 0xffffull) > 1 || __builtin_amdgcn_readlane((int)e.z, w) > 1 ||
-        M < kCodeSure) {
-      // exact keys of the codes near the largest
-      double bk = 0.0;
-      uint32_t bp = 0x7fffffffu;
-      if (mx >= T)
-        for (int u = 0; u < per; ++u) {
-          const uint32_t v = tile[u];
-          if (v < T) continue;
-          const uint32_t i = (uint32_t)((tid << ts) + u);
-          double K;
-          if (v & kCodeExact) {
-            K = load_at(I->key, i * 8u);
-          } else {
-            const double2 h = load_at(I->h, i * 16u);
-            K = switching_key_far((v & kCodeDown) ? -1 : 1, h.x, h.y, load_at(I->hk, i * 8u), P.b,
-                                  P.c, P.ep, P.eq);
-            store_at(I->key, i * 8u, K);
-            tile[u] = K > 0.0 ? v | kCodeExact : 0u;
-            touched[tid] = 1u;
-          }
-          if (better(K, i, bk, bp)) {
-            bk = K;
-            bp = i;
-          }
-        }
-      // largest key, lowest index, over the wavefront and then the workgroup
-      const double wk = wave_max_f64(bk);
-      const uint32_t wi = ~wave_max_u32(bk == wk ? ~bp : 0u);
-      if (lane == 0) {
-        sh.rk[wave] = wk;
-        sh.ri[wave] = wi;
-      }
-      __syncthreads();
-      const int ql = lane & 15;
-      const double ek = ql < (NT >> 6) ? sh.rk[ql] : 0.0;
-      const uint32_t ei = ql < (NT >> 6) ? sh.ri[ql] : 0x7fffffffu;
-      const double rk = wave_max_f64(ek);
-      if (!(rk > 0.0)) continue;  // none of them can flip: the next codes
-      j = (int32_t)~wave_max_u32(ek == rk ? ~ei : 0u);
-      M = code[j];
-    }
-    if (deadline && sh.pause) {
-      status = 1;
-      break;
-    }
-    if (flips >= max_flips) {
-      status = -5;
-      break;
-    }
-    const bool down = (__builtin_amdgcn_readfirstlane((int)M) & kCodeDown) != 0u;
-    const double two = down ? 2.0 : -2.0;  // 2 s_new
-    const int64_t row = (int64_t)j * D;
-    const ASI_GLOBAL int32_t* const rc = I->rcol + row;
-    const ASI_GLOBAL double* const ra = I->rA + row;
-    const ASI_GLOBAL double* const rb = I->rBr + row;
-    for (int k = tid; k < D; k += NT) {
-      // the slot's column and couplings together (a padding slot holds -1 and
-      // zeros), then the neighbour's state: two round trips
-      const int32_t i0 = load_at(rc, (uint32_t)k * 4u);
-      const double ca = load_at(ra, (uint32_t)k * 8u);
-      const double cb = load_at(rb, (uint32_t)k * 8u);
-      const uint32_t i = (uint32_t)max(i0, 0);
-      const double2 hi = load_at(I->h, i * 16u);
-      const double hki = load_at(I->hk, i * 8u);
-      const double2 di = (mode == kFieldCarry) ? load_at(I->hd, i * 16u) : make_double2(0.0, 0.0);
-      const bool neg = (spin[i >> 5] >> (i & 31u)) & 1u;
-      const double da = two * ca, db = two * cb;
-      const double hp = hi.x + da, hq = hi.y + db;
-      const uint32_t v = key_code(neg, hp, hq, hki, P);
-      if (i0 >= 0) {
-        code[i] = v;
-        touched[i >> ts] = 1u;
-        store_at(I->h, i * 16u, make_double2(hp, hq));
-        if (mode == kFieldCarry)
-          store_at(I->hd, i * 16u, make_double2(di.x + da, di.y + db));
-        else if (mode == kFieldDirty)
-          store_at(I->dirty, i, (uint8_t)1);
-      }
-    }
-    if (tid == 0) {
-      code[j] = 0u;
-      touched[j >> ts] = 1u;
-      flipped = j;
-      store_at(I->s, (uint32_t)j, down ? (int8_t)1 : (int8_t)-1);
-      if (logpos < I->log_cap) {
-        I->log_t[logpos] = (int32_t)t;
-        I->log_j[logpos] = j;
-      }
-      hash = (hash ^ (((uint64_t)(uint32_t)t << 32) | (uint64_t)(uint32_t)j)) * 0x100000001b3ull;
-    }
-    ++logpos;
-    ++flips;
-    __syncthreads();
-  }
-  return status;
-}
-
 // Per-64-row maxima of the stored keys -- the lowest level of the relax
 // tree -- rebuilt by the whole workgroup, four 64-row groups per wavefront
 // at a time (their loads issued together).
@@ -2431,61 +2235,454 @@ __device__ __forceinline__ void rebuild_t1(const InstDev* __restrict__ I) {
   __syncthreads();
 }
 
-// Relax one instance at step t (Sec. II.H) and advance its run cursor.
-// kPathLds: one flip at a time, the keys in LDS.  kPathSpec: steps that start
-// with at least spec_min flippable magnets (and a degree that leaves room for
-// batches) take the speculative path; the others the max tree; a speculative
-// step whose batches stay small continues on the tree; a paused step resumes
-// on the path it was on.  kPathTree: the max tree alone.  All flip exactly the
-// magnets, in exactly the order, of the one-at-a-time relax.  Each path is a
-// kernel of its own, so that its registers are allocated for that path.
-template <int kPath>
-struct RelaxState {
-  RelaxShared tree;
-  SpecShared spec;
-};
-template <>
-struct RelaxState<kPathTree> {
-  RelaxShared tree;
-};
-template <>
-struct RelaxState<kPathLds> {
-  FlipShared flip;
+// ------------------------------------------------------------ relax, keys in LDS
+// One-at-a-time relax for instances whose keys fit in LDS (kLdsMaxN magnets):
+// the code of every magnet, a spin bit per magnet, and per wavefront the best
+// code of the magnets its threads own.
+// A thread owns one tile of consecutive magnets: an odd multiple of 4 of them
+// (so that the 16-byte reads of neighbouring threads' tiles meet different LDS
+// banks), as few as cover the instance.
+__host__ __device__ inline int flip_tile(int64_t n, int threads) {
+  const int chunks = (int)((n + 4 * threads - 1) / (4 * threads));
+  return 4 * (chunks | 1);
+}
+
+__host__ __device__ inline size_t flip_lds_bytes(int64_t n, int threads) {
+  const int per = flip_tile(n, threads);
+  const size_t tiles = (size_t)((n + per - 1) / per);
+  return tiles * per * 4 + align16((size_t)((n + 31) / 32) * 4) + (size_t)threads * 4;
+}
+
+struct FlipShared {
+  uint2 best[kMaxRelaxWaves];  // per wavefront: code, its tile << 8 | codes near it
+  double rk[kMaxRelaxWaves];   // resolving a near-tie: per wavefront exact key and index
+  uint32_t ri[kMaxRelaxWaves]; //   (index << 1 | sign bit; bit 31: an unknown key became known)
+  int pause;
 };
 
+// A global load at a 32-bit byte offset from a uniform base.
+template <class T>
+__device__ __forceinline__ T load_at(const ASI_GLOBAL T* base, uint32_t bytes) {
+  return *(const ASI_GLOBAL T*)((const ASI_GLOBAL char*)base + bytes);
+}
+template <class T>
+__device__ __forceinline__ void store_at(ASI_GLOBAL T* base, uint32_t bytes, T v) {
+  *(ASI_GLOBAL T*)((ASI_GLOBAL char*)base + bytes) = v;
+}
+
+// A launch's parts that are not its hot loop are called out of line, so that
+// each part's registers are allocated for itself: inlined into one kernel, the
+// relax with keys in LDS took 2.6 us a flip instead of 2.1.
+// What a relax reads and advances, in LDS while it is called out of line.
+struct RelaxCount {
+  int64_t flips, logpos;
+  uint64_t hash;
+};
+
+union RelaxParts {
+  RelaxShared tree;
+  SpecShared spec;
+  FlipShared flip;
+};
+struct RelaxState {
+  RelaxCount c;
+  RelaxParts u;
+};
+
+// Relax at step t, one flip at a time.  Each thread owns a tile of
+// consecutive magnets and keeps its largest code in a register.  Per flip:
+//   - the wavefronts' best codes give the winner, whose row is loaded.  If no
+//     other code lies within kCodeNear of it, and it is surely above 1, it is
+//     the magnet the exact keys would pick; else the exact FP64 keys of the
+//     codes that near decide (keys of 0 are struck out, equal keys go to the
+//     lower index); an exact key is kept in the key array until the magnet's
+//     field changes;
+//   - the threads update the neighbours' fields and codes;  [barrier]
+//   - the owners of changed tiles rescan them in LDS and their wavefronts
+//     renew their best.  [barrier]
+// The last wavefront, which updates no neighbour below 960 of them, does the
+// flip's bookkeeping.
+// What bounds it: one dependent chain per flip -- the flipped magnet's row,
+// then its neighbours' fields (two round trips to memory, ~1,100 of ~3,500
+// cycles), two barriers, three LDS round trips, and the instructions between
+// them, which issue one by one (about eight cycles each).  Against the max
+// tree it leaves out of that chain the FP64 powers (~200 dependent
+// instructions each; exact keys are evaluated for 1-8 % of the flips), the
+// rescans of tiles in memory and three of five barriers: per flip 6.2 -> 1.5
+// us on a 5,100-magnet anneal at 632 neighbours, 5.6 -> 1.9 on a
+// 20,200-magnet reversal at 632, 5.1 -> 1.7 on a 29,040-magnet reversal at
+// 60; with every key tied (no disorder) 5.1 -> 1.3.  Tried and slower: the
+// runner-up's row loaded ahead (right for 20-80 % of the flips; its loads
+// return before the neighbours' can), tiles dealt to the wavefronts in turn
+// (more wavefronts rescan), a changed tile rescanned by half a wavefront.
+// Returns as relax_tree.
+template <bool kTile1>
+__device__ __forceinline__ int relax_lds(const InstDev* __restrict__ I, int64_t t, unsigned char* lds_raw,
+                                         RelaxState& st, int64_t ncand, bool from_pool,
+                                         uint64_t deadline) {
+  if (from_pool && ncand == 0) return 0;  // nothing can flip
+  FlipShared& sh = st.u.flip;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int NT = blockDim.x;
+  const bool clerk = tid == NT - 64;
+  const int32_t n = (int32_t)I->n;
+  const int NW = NT >> 6;
+  const int per = kTile1 ? 4 : flip_tile(n, NT), nc = per >> 2;
+  // tile of magnet i: i / per, exact for i < 2^16 and per <= 64
+  const uint32_t per_inv = 0xffffffffu / (uint32_t)per + 1u;
+  auto tile_of = [&](uint32_t i) { return __umulhi(i, per_inv); };
+  const int32_t npad = (int32_t)((n + per - 1) / per) * per;
+  uint32_t* const code = (uint32_t*)lds_raw;
+  uint32_t* const spin = code + npad;  // bit per magnet: spin -1
+  // per tile: a code of it changed
+  uint32_t* const touched = (uint32_t*)((unsigned char*)spin + align16((size_t)((n + 31) / 32) * 4));
+
+  const int32_t D = I->D;
+  const int32_t mode = I->field_mode;
+  const bool carry = mode == kFieldCarry;
+  const KeyPar P = key_par(I);
+  const int64_t left0 = I->max_flips - uniform(st.c.flips);  // flips this call may make
+  const int64_t logpos = uniform(st.c.logpos);
+  uint64_t hash = st.c.hash;
+  int64_t done = 0;
+  const ASI_GLOBAL int32_t* const rcol = I->rcol;
+  const ASI_GLOBAL double2* const rAB = I->rAB;
+  ASI_GLOBAL double2* const hh = I->h;
+  ASI_GLOBAL double2* const hd = I->hd;
+  const ASI_GLOBAL double* const ghk = I->ghk;
+
+  for (int q = tid; q < npad / 4; q += NT) ((uint4*)code)[q] = make_uint4(0u, 0u, 0u, 0u);
+  // sign bits of 32 spins per word, from four 8-byte loads (the array's
+  // allocation is a multiple of 256 bytes)
+  for (int q = tid; q < (n + 31) / 32; q += NT) {
+    const ASI_GLOBAL uint64_t* s8 = (const ASI_GLOBAL uint64_t*)I->s + 4 * (int64_t)q;
+    uint64_t v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = (8 * (4 * q + u) < n) ? s8[u] : 0ull;
+    uint32_t w = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      w |= (uint32_t)((((v[u] >> 7) & 0x0101010101010101ull) * 0x0102040810204080ull) >> 56) << (8 * u);
+    spin[q] = w;
+  }
+  touched[tid] = 0u;
+  if (tid < kMaxRelaxWaves) sh.best[tid] = make_uint2(0u, 0u);
+  if (tid == 0) sh.pause = 0;
+  __syncthreads();
+  auto put = [&](uint32_t i, double key, bool neg) {  // the key array holds this key
+    const uint32_t tl = tile_of(i);
+    code[i] = code_of_key(key, neg) | kCodeExact | (i - tl * (uint32_t)per);
+    touched[tl] = 1u;
+  };
+  if (from_pool) {  // the field phase's list of flippable magnets
+    for (int64_t q = tid; q < ncand; q += NT) {
+      const uint32_t pay = I->cpay[0][q];
+      put(pay & 0x7fffffffu, I->ckey[0][q], (pay >> 31) != 0u);
+    }
+  } else {  // the key array, which the speculative relax keeps exact
+    for (int32_t i = tid; i < n; i += NT) {
+      const double key = load_at(I->key, (uint32_t)i * 8u);
+      if (key > 0.0) put((uint32_t)i, key, load_at(I->s, (uint32_t)i) < 0);
+    }
+  }
+  __syncthreads();
+
+  // The thread's slot of a flip: slot tid of the flipped magnet's row (a
+  // padding slot holds column -1 and zeros) and the neighbour's state.
+  struct Slot {
+    int32_t i0;
+    double2 ab, h, d;
+    double g;
+  };
+  auto load_row = [&](int32_t j, int k, int32_t& i0, double2& ab) {
+    const uint32_t e = (uint32_t)j * (uint32_t)D + (uint32_t)k;  // n * D * 16 < 2^32
+    i0 = load_at(rcol, e * 4u);
+    ab = load_at(rAB, e * 16u);
+  };
+  auto load_state = [&](Slot& q) {
+    const uint32_t i = (uint32_t)max(q.i0, 0);
+    q.h = load_at(hh, i * 16u);
+    q.g = load_at(ghk, i * 8u);
+    if (carry) q.d = load_at(hd, i * 16u);
+  };
+  // The neighbour's new field and code; the carried sum, which nothing waits
+  // for, last.
+  auto change = [&](const Slot& q, double two) {
+    const uint32_t i = (uint32_t)max(q.i0, 0);
+    const bool neg = (spin[i >> 5] >> (i & 31u)) & 1u;
+    const double da = two * q.ab.x, db = two * q.ab.y;
+    const double hp = q.h.x + da, hq = q.h.y + db;
+    const uint32_t v = key_code(neg, hp, hq, q.g, P);
+    if (q.i0 >= 0) {
+      const uint32_t tl = tile_of(i);
+      code[i] = v ? v | (i - tl * (uint32_t)per) : 0u;
+      if (!kTile1) touched[tl] = 1u;
+      store_at(hh, i * 16u, make_double2(hp, hq));
+      if (carry)
+        store_at(hd, i * 16u, make_double2(q.d.x + da, q.d.y + db));
+      else if (mode == kFieldDirty)
+        store_at(I->dirty, i, (uint8_t)1);
+    }
+  };
+
+  // Flip j (down: its spin is -1), its row's slots of this thread loaded in q.
+  int32_t j = -1;  // last flipped magnet (its spin bit toggled by the clerk later)
+  auto flip = [&](Slot& q, bool down) {
+    const double two = down ? 2.0 : -2.0;  // 2 s_new
+    if (tid < D) change(q, two);
+    for (int k = tid + NT; k < D; k += NT) {
+      load_row(j, k, q.i0, q.ab);
+      load_state(q);
+      change(q, two);
+    }
+    if (clerk) {
+      code[j] = 0u;
+      if (!kTile1) touched[tile_of((uint32_t)j)] = 1u;
+      store_at(I->s, (uint32_t)j, down ? (int8_t)1 : (int8_t)-1);
+      if (logpos + done < I->log_cap) {
+        I->log_t[logpos + done] = (int32_t)t;
+        I->log_j[logpos + done] = j;
+      }
+      hash = (hash ^ (((uint64_t)(uint32_t)t << 32) | (uint64_t)(uint32_t)j)) * 0x100000001b3ull;
+    }
+    ++done;
+    __syncthreads();
+  };
+
+  uint32_t* const tile = code + tid * per;
+  uint32_t mx = 0;  // largest code of the thread's tile
+  int status = 0;
+  bool stop = false;
+  while (true) {
+    uint32_t Mv;  // the largest code
+    while (true) {
+      // owners of changed tiles (tiles of four codes: every owner, which is
+      // cheaper than flags)
+      const bool mine = kTile1 ? tid < npad / 4 : touched[tid] != 0u;
+      if (__ballot(mine)) {
+        uint32_t near_mx = 0;  // tiles of four: codes near the largest
+        if (mine) {
+          const uint4* const c4 = (const uint4*)tile;
+          if (kTile1) {
+            const uint4 c = c4[0];
+            mx = max(max(c.x, c.y), max(c.z, c.w));
+            const uint32_t T = code_floor(mx);
+            near_mx = (c.x >= T) + (c.y >= T) + (c.z >= T) + (c.w >= T);
+          } else {
+            touched[tid] = 0u;
+            mx = 0;
+            for (int u0 = 0; u0 < nc; u0 += 5) {
+              // five 16-byte reads at a time, the last one again past the end
+              uint4 c[5];
+#pragma unroll
+              for (int u = 0; u < 5; ++u) c[u] = c4[min(u0 + u, nc - 1)];
+#pragma unroll
+              for (int u = 0; u < 5; ++u) mx = max(mx, max(max(c[u].x, c[u].y), max(c[u].z, c[u].w)));
+            }
+          }
+        }
+        // the wavefront's best; codes near it: one per lane, and the others of
+        // the best lane's tile
+        const uint32_t m = wave_max_u32(mx);
+        const uint32_t T = code_floor(m);
+        uint32_t cnt = (uint32_t)__popcll(__ballot(mx >= T)) - 1u;
+        if (kTile1) {
+          cnt += near_mx;
+        } else {
+          const int wl = __ffsll((unsigned long long)__ballot(mx == m)) - 1;
+          const uint32_t v = lane < per ? code[(wave * 64 + wl) * per + lane] : 0u;
+          cnt += (uint32_t)__popcll(__ballot(v >= T));
+        }
+        if (mx == m) sh.best[wave] = make_uint2(m, (uint32_t)tid << 8 | (cnt & 255u));
+      }
+      if (clerk) {
+        if (j >= 0) atomicXor(&spin[j >> 5], 1u << (j & 31));
+        if (deadline) sh.pause = (done > 0 && (done & 15) == 0 && past(deadline)) ? 1 : 0;
+      }
+      __syncthreads();
+      const uint2 e = sh.best[lane & 15];
+      Mv = row_max_u32(e.x);
+      // the wavefronts whose best is near the largest: normally one
+      const uint32_t near = (uint32_t)__ballot(e.x >= code_floor(Mv)) & 0xffffu;
+      const int w = __ffs(near) - 1;
+      const uint32_t M = (uint32_t)__builtin_amdgcn_readlane((int)e.x, w);
+      const uint32_t meta = (uint32_t)__builtin_amdgcn_readlane((int)e.y, w);
+      j = (int32_t)(meta >> 8) * per + (int32_t)(M & kCodePlace);
+      // near ties, a key that may be below 1, and the end (no code: near == 0)
+      if ((near & (near - 1u)) != 0u || near == 0u || (meta & 255u) != 1u || M < kCodeSure ||
+          M >= kCodeUnknown)
+        break;
+      Slot q;
+      if (tid < D) {
+        load_row(j, tid, q.i0, q.ab);
+        load_state(q);
+      }
+      stop = done >= left0 || (deadline && sh.pause);
+      if (stop) break;
+      flip(q, (M & kCodeDown) != 0u);
+    }
+    Mv = (uint32_t)__builtin_amdgcn_readfirstlane((int)Mv);
+    if (stop || Mv == 0u) break;
+    // exact keys of the codes near the largest
+    const uint32_t T = code_floor(Mv);
+    double bk = 0.0;
+    uint32_t bp = 0x7fffffffu;  // index | sign bit
+    bool unknown = false;
+    if (mx >= T) {
+      uint64_t at = 0;  // their places in the tile
+      for (int u = 0; u < nc; ++u) {
+        const uint4 c = ((const uint4*)tile)[u];
+        at |= (uint64_t)((c.x >= T ? 1u : 0u) | (c.y >= T ? 2u : 0u) | (c.z >= T ? 4u : 0u) |
+                         (c.w >= T ? 8u : 0u)) << (4 * u);
+      }
+      while (at) {
+        const int u = __ffsll((unsigned long long)at) - 1;
+        at &= at - 1ull;
+        const uint32_t c = tile[u];
+        const uint32_t i = (uint32_t)(tid * per + u);
+        const bool neg = (c & kCodeDown) != 0u;
+        double K;
+        if (c & kCodeExact) {
+          K = load_at(I->key, i * 8u);
+        } else {
+          const double2 h = load_at(hh, i * 16u);
+          K = switching_key_far(I, neg, h.x, h.y, load_at(I->hk, i * 8u));
+          store_at(I->key, i * 8u, K);
+          tile[u] = K > 0.0 ? code_of_key(K, neg) | kCodeExact | (uint32_t)u : 0u;
+          if (!kTile1) touched[tid] = 1u;
+          unknown |= c >= kCodeUnknown;
+        }
+        const uint32_t pay = i | (neg ? 0x80000000u : 0u);
+        if (better(K, pay, bk, bp)) {
+          bk = K;
+          bp = pay;
+        }
+      }
+    }
+    // largest key, lowest index, over the wavefront and then the workgroup (the
+    // index above the sign: ~(index << 1 | sign) is largest for the lowest index)
+    const double wk = wave_max_f64(bk);
+    const uint32_t wi = ~wave_max_u32(bk == wk ? ~(bp << 1 | bp >> 31) : 0u) & 0x7fffffffu;
+    const bool wu = __ballot(unknown) != 0ull;
+    if (lane == 0) {
+      sh.rk[wave] = wk;
+      sh.ri[wave] = wi | (wu ? 0x80000000u : 0u);
+    }
+    __syncthreads();
+    const int ql = lane & 15;
+    const double ek = ql < NW ? sh.rk[ql] : 0.0;
+    const uint32_t ei = ql < NW ? sh.ri[ql] : 0u;
+    const double rk = wave_max_f64(ek);
+    // none of them can flip, or one's place in the order was unknown until now:
+    // choose again by the new codes
+    j = -1;
+    if (!(rk > 0.0) || __ballot((ei >> 31) != 0u) != 0ull) continue;
+    stop = done >= left0 || (deadline && sh.pause);
+    if (stop) break;
+    const uint32_t jx = ~wave_max_u32(ek == rk ? ~ei : 0u);
+    j = (int32_t)(jx >> 1);
+    Slot q;
+    if (tid < D) {
+      load_row(j, tid, q.i0, q.ab);
+      load_state(q);
+    }
+    flip(q, (jx & 1u) != 0u);
+  }
+  if (stop) status = deadline && sh.pause ? 1 : -5;
+  if (clerk) {
+    st.c.flips += done;
+    st.c.logpos = logpos + done;
+    st.c.hash = hash;
+  }
+  __syncthreads();
+  return status;
+}
+
+extern __shared__ __align__(16) unsigned char lds_dyn[];
+
+__device__ __forceinline__ int run_spec(const InstDev* I, int64_t t, RelaxState* st, int64_t ncand,
+                                       uint64_t deadline) {
+  int64_t flips = uniform(st->c.flips), logpos = uniform(st->c.logpos);
+  uint64_t hash = (uint64_t)uniform((int64_t)st->c.hash);
+  const int status = relax_spec(I, t, lds_dyn, st->u.spec, ncand, flips, logpos, hash, deadline);
+  __syncthreads();
+  if (threadIdx.x == 0) st->c = RelaxCount{flips, logpos, hash};
+  __syncthreads();
+  return status;
+}
+
+__device__ __attribute__((noinline)) int call_spec(const InstDev* I, int64_t t, ASI_LDS RelaxState* st,
+                                                   int64_t ncand, uint64_t deadline) {
+  return run_spec(uniform(I), uniform(t), (RelaxState*)st, uniform(ncand),
+                  (uint64_t)uniform((int64_t)deadline));
+}
+
+template <bool kFlatOk>
+__device__ __forceinline__ int run_tree(const InstDev* I, int64_t t, RelaxState* st, bool rebuild,
+                                       uint64_t deadline) {
+  if (rebuild) rebuild_t1(I);
+  int64_t flips = uniform(st->c.flips), logpos = uniform(st->c.logpos);
+  uint64_t hash = (uint64_t)uniform((int64_t)st->c.hash);
+  const int status = relax_tree<kFlatOk>(I, t, lds_dyn, st->u.tree, flips, logpos, hash, deadline);
+  __syncthreads();
+  if (threadIdx.x == 0) st->c = RelaxCount{flips, logpos, hash};
+  __syncthreads();
+  return status;
+}
+
+// The field phase of a whole instance by one workgroup.
+__device__ __attribute__((noinline)) void call_field(const InstDev* I0, int64_t t, bool resume) {
+  const InstDev* I = uniform(I0);
+  const int wave = threadIdx.x >> 6, NW = blockDim.x >> 6;
+  for (int64_t row0 = (int64_t)wave * 64; row0 < I->n; row0 += (int64_t)NW * 64)
+    field_rows64_pool(I, row0, uniform(t), resume);
+  __syncthreads();
+}
+
+// Relax one instance at step t (Sec. II.H) and advance its run cursor.
+// Steps that start with enough flippable magnets (spec_min, and a degree that
+// leaves room for batches) take the speculative path; the others, and a
+// speculative step whose batches stay small, go one flip at a time: with every
+// key in LDS where they fit (kPathLds, kPathLdsSpec), else on the max tree
+// (kPathTree, kPathSpec).  A paused step resumes on the path it was on.  All
+// flip exactly the magnets, in exactly the order, of the one-at-a-time relax.
 template <int kPath>
 __device__ __forceinline__ int relax_step(const InstDev* __restrict__ I, RunDev* __restrict__ R, int64_t t,
-                          unsigned char* lds_raw, RelaxState<kPath>& sh, uint64_t deadline) {
+                          RelaxState& st, uint64_t deadline) {
+  constexpr bool kLds = kPath == kPathLds || kPath == kPathLdsSpec;
   const int64_t ncand = __hip_atomic_load(I->ccount, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const int64_t acc0 = R->step_acc;  // flips of step t before a pause
-  int64_t flips = acc0;
-  int64_t logpos = R->flips;
-  uint64_t hash = R->hash;
+  if (threadIdx.x == 0) st.c = RelaxCount{acc0, R->flips, R->hash};
+  __syncthreads();
   bool spec = false;
-  int status;
+  int status = 2;
   if ((int64_t)(uint32_t)ncand > I->ccap) {
     status = kPoolOverflow;  // cannot happen while every pass starts from an empty pool
-  } else if constexpr (kPath == kPathLds) {
-    status = relax_lds(I, t, lds_raw, sh.flip, ncand, flips, logpos, hash, deadline);
-  } else if constexpr (kPath == kPathTree) {
-    status = relax_tree<true>(I, t, lds_raw, sh.tree, flips, logpos, hash, deadline);
   } else {
-    spec = blockDim.x == 1024 &&
-           (R->paused ? R->spec != 0 : (I->D <= kSpecMaxD && ncand >= I->spec_min));
-    status = 2;
-    if (spec) status = relax_spec(I, t, lds_raw, sh.spec, ncand, flips, logpos, hash, deadline);
+    if constexpr (kPath == kPathSpec || kPath == kPathLdsSpec) {
+      spec = blockDim.x == 1024 &&
+             (R->paused ? R->spec != 0 : (I->D <= kSpecMaxD && ncand >= I->spec_min));
+      if (spec)
+        status = kLds ? call_spec(I, t, (ASI_LDS RelaxState*)&st, ncand, deadline)
+                      : run_spec(I, t, &st, ncand, deadline);
+    }
     if (status == 2) {
-      if (spec) rebuild_t1(I);  // the keys have moved since the field phase
+      if constexpr (kLds)
+        status = flip_tile(I->n, (int)blockDim.x) == 4
+                     ? relax_lds<true>(I, t, lds_dyn, st, ncand, !spec, deadline)
+                     : relax_lds<false>(I, t, lds_dyn, st, ncand, !spec, deadline);
+      else
+        status = run_tree<kPath == kPathTree>(I, t, &st, spec, deadline);
       spec = false;
-      status = relax_tree<false>(I, t, lds_raw, sh.tree, flips, logpos, hash, deadline);
     }
   }
   __syncthreads();
   if (threadIdx.x == 0) {
     __hip_atomic_store(I->ccount, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int64_t flips = st.c.flips;
     R->flips += flips - acc0;
     R->flips_call += flips - acc0;
-    R->hash = hash;
+    R->hash = st.c.hash;
     if (status == 1) {
       R->step_acc = flips;
       R->paused = 1;
@@ -2505,6 +2702,11 @@ __device__ __forceinline__ int relax_step(const InstDev* __restrict__ I, RunDev*
   return status;
 }
 
+// Whether an instance is relaxed by launches on `path`.
+__device__ __forceinline__ bool on_path(const InstDev* I, int path) {
+  return (I->lds_keys != 0) == (path == kPathLds || path == kPathLdsSpec);
+}
+
 template <int kPath>
 __global__ __launch_bounds__(64 * kMaxRelaxWaves) void k_relax(const InstDev* __restrict__ insts,
                                                               RunDev* __restrict__ runs) {
@@ -2513,10 +2715,9 @@ __global__ __launch_bounds__(64 * kMaxRelaxWaves) void k_relax(const InstDev* __
   // structures rebuilt by the preceding field launch
   if (!R->active && !R->paused) return;
   const InstDev* I = insts + blockIdx.x;
-  if ((I->lds_keys != 0) != (kPath == kPathLds)) return;  // relaxed by another launch
-  extern __shared__ unsigned char lds_raw[];
-  __shared__ RelaxState<kPath> sh;
-  relax_step<kPath>(I, R, R->t, lds_raw, sh, 0);
+  if (!on_path(I, kPath)) return;  // relaxed by another launch
+  __shared__ RelaxState st;
+  relax_step<kPath>(I, R, R->t, st, 0);
 }
 
 // One workgroup per instance runs whole field steps -- its own field phase,
@@ -2538,29 +2739,21 @@ __global__ __launch_bounds__(64 * kMaxRelaxWaves) void k_fused(const InstDev* __
   const bool paused = R->paused != 0;
   if (!R->active && !paused) return;
   const InstDev* I = insts + blockIdx.x;
-  if ((I->lds_keys != 0) != (kPath == kPathLds)) return;  // run by another launch
-  extern __shared__ unsigned char lds_raw[];
-  __shared__ RelaxState<kPath> sh;
+  if (!on_path(I, kPath)) return;  // run by another launch
+  __shared__ RelaxState st;
   __shared__ int go;
-  const int wave = threadIdx.x >> 6, NW = blockDim.x >> 6;
   const uint64_t t_start = wall_clock64();
   const uint64_t deadline = budget_ticks > 0 ? t_start + (uint64_t)budget_ticks : 0;
   bool ready = first_ready != 0;
   if (paused && !ready) {
-    for (int64_t row0 = (int64_t)wave * 64; row0 < I->n; row0 += (int64_t)NW * 64)
-      field_rows64_pool(I, row0, R->t, true);
-    __syncthreads();
+    call_field(I, R->t, true);
     ready = true;
   }
   for (int64_t k = 0; k < max_steps; ++k) {
     const int64_t t = R->t;
-    if (!ready) {
-      for (int64_t row0 = (int64_t)wave * 64; row0 < I->n; row0 += (int64_t)NW * 64)
-        field_rows64_pool(I, row0, t);
-      __syncthreads();
-    }
+    if (!ready) call_field(I, t, false);
     ready = false;
-    if (relax_step<kPath>(I, R, t, lds_raw, sh, deadline) != 0) break;
+    if (relax_step<kPath>(I, R, t, st, deadline) != 0) break;
     if (threadIdx.x == 0) go = (R->active && !past(deadline)) ? 1 : 0;
     __syncthreads();
     if (!go) break;
@@ -3058,6 +3251,10 @@ void launch_draw_hk(double* hk, int64_t n, double mean, double k, uint64_t seed,
                      seed);
 }
 
+void launch_inverse_hk(const double* hk, int64_t n, double b, double* g, hipStream_t st) {
+  hipLaunchKernelGGL(k_inverse_hk, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, hk, n, b, g);
+}
+
 void launch_neighbour_count(const double* x, const double* y, const int32_t* cellx,
                             const int32_t* celly, const int32_t* cell_start,
                             const int32_t* cell_members, int64_t n, int64_t gx, int64_t gy,
@@ -3072,13 +3269,11 @@ void launch_neighbour_fill(const double* x, const double* y, const double* mx, c
                            const int32_t* cellx, const int32_t* celly, const int32_t* cell_start,
                            const int32_t* cell_members, int64_t n, int64_t gx, int64_t gy,
                            double cut2, double alpha, int32_t D, int32_t* col, double* A,
-                           double* B, int32_t* rcol, double* rA, double* rBr,
-                           hipStream_t st) {
+                           double* B, int32_t* rcol, double2* rAB, hipStream_t st) {
   const int bs = 128;
   const int64_t nb = (n + bs - 1) / bs;
   hipLaunchKernelGGL(k_nb_fill, dim3((unsigned)nb), dim3(bs), 0, st, x, y, mx, my, cellx, celly,
-                     cell_start, cell_members, n, gx, gy, cut2, alpha, D, col, A, B, rcol, rA,
-                     rBr);
+                     cell_start, cell_members, n, gx, gy, cut2, alpha, D, col, A, B, rcol, rAB);
 }
 
 void launch_field(const InstDev* insts, RunDev* runs, const int32_t* blk_inst,
@@ -3126,6 +3321,8 @@ void launch_relax(const InstDev* insts, RunDev* runs, int32_t count, int32_t wav
   const dim3 g((unsigned)count), b((unsigned)(64 * waves));
   if (path == kPathLds)
     hipLaunchKernelGGL(k_relax<kPathLds>, g, b, lds_bytes, st, insts, runs);
+  else if (path == kPathLdsSpec)
+    hipLaunchKernelGGL(k_relax<kPathLdsSpec>, g, b, lds_bytes, st, insts, runs);
   else if (path == kPathTree)
     hipLaunchKernelGGL(k_relax<kPathTree>, g, b, lds_bytes, st, insts, runs);
   else
@@ -3139,6 +3336,9 @@ void launch_fused(const InstDev* insts, RunDev* runs, int32_t count, int32_t wav
   const dim3 g((unsigned)count), b((unsigned)(64 * waves));
   if (path == kPathLds)
     hipLaunchKernelGGL(k_fused<kPathLds>, g, b, lds_bytes, st, insts, runs, max_steps,
+                       budget_ticks, first_ready);
+  else if (path == kPathLdsSpec)
+    hipLaunchKernelGGL(k_fused<kPathLdsSpec>, g, b, lds_bytes, st, insts, runs, max_steps,
                        budget_ticks, first_ready);
   else
     hipLaunchKernelGGL(k_fused<kPathSpec>, g, b, lds_bytes, st, insts, runs, max_steps,
@@ -3163,7 +3363,10 @@ size_t relax_lds_bytes(int64_t n, int32_t l1_shift) {
   return a > b ? a : b;
 }
 
-size_t relax_keys_lds_bytes(int64_t n, int32_t waves) { return flip_lds_bytes(n, 64 * waves); }
+size_t relax_keys_lds_bytes(int64_t n, int32_t waves, bool spec) {
+  const size_t a = flip_lds_bytes(n, 64 * waves);
+  return spec ? std::max(a, spec_lds_bytes()) : a;
+}
 
 hipError_t configure_kernels() {
   // the relax kernels take more than 64 KB of dynamic LDS
@@ -3173,6 +3376,8 @@ hipError_t configure_kernels() {
       {reinterpret_cast<const void*>(&k_relax<kPathTree>), tree},
       {reinterpret_cast<const void*>(&k_relax<kPathSpec>), tree},
       {reinterpret_cast<const void*>(&k_relax<kPathLds>), keys},
+      {reinterpret_cast<const void*>(&k_relax<kPathLdsSpec>), keys},
+      {reinterpret_cast<const void*>(&k_fused<kPathLdsSpec>), keys},
       {reinterpret_cast<const void*>(&k_fused<kPathSpec>), tree},
       {reinterpret_cast<const void*>(&k_fused<kPathLds>), keys}};
   hipError_t e = hipSuccess;

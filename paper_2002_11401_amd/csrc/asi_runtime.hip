@@ -273,6 +273,7 @@ size_t footprint_estimate(int64_t n, int64_t D, int64_t K, int64_t log_cap) {
   size_t b = slots * (4 + 8 + 8) + (size_t)n * (size_t)std::max<int64_t>(D, 1) * (4 + 8 + 8);
   b += (size_t)n * (4 + 8 + 8 + 8 + 1 + 1 + 8 * 7 + 4) + (size_t)(n + 8192) * 32;
   b += (size_t)nsl * 12 + (size_t)log_cap * 8 + (size_t)K * 20;
+  if (n <= kLdsMaxN) b += 8 * (size_t)n;
   if (D >= kHdMinD && nsl < kHdSplitSlices) b += (size_t)n * (size_t)((D + 63) / 64) * 16;
   b += 1 << 16;
   return b;
@@ -280,10 +281,11 @@ size_t footprint_estimate(int64_t n, int64_t D, int64_t K, int64_t log_cap) {
 
 // Relax path and dynamic LDS of the handle's current shapes.
 void set_relax_path(asi_sim* s) {
-  const bool in_lds = relax_keys_in_lds(s->n, s->D, s->relax_waves, s->hI.spec_min);
-  s->hI.lds_keys = in_lds ? 1 : 0;
-  s->path = in_lds ? kPathLds : relax_may_speculate(s->D, s->relax_waves) ? kPathSpec : kPathTree;
-  s->lds = in_lds ? relax_keys_lds_bytes(s->n, s->relax_waves) : relax_lds_bytes(s->n, s->l1s);
+  const bool keys = relax_keys_in_lds(s->hI, s->relax_waves);
+  const bool spec = relax_may_speculate(s->D, s->relax_waves);
+  s->hI.lds_keys = keys ? 1 : 0;
+  s->path = relax_path(keys, spec);
+  s->lds = keys ? relax_keys_lds_bytes(s->n, s->relax_waves, spec) : relax_lds_bytes(s->n, s->l1s);
 }
 
 asi_status create_impl(const asi_params* p, const asi_device* dev, asi_sim* s) {
@@ -401,9 +403,8 @@ asi_status create_impl(const asi_params* p, const asi_device* dev, asi_sim* s) {
   // row-major copy for the relax (every slot written by the fill)
   const size_t rslots = (size_t)n * (size_t)std::max(D, 1);
   int32_t* drcol = dalloc<int32_t>(s, rslots);
-  double* drA = dalloc<double>(s, rslots);
-  double* drBr = dalloc<double>(s, rslots);
-  if (!dcol || !dA || !dB || !drcol || !drA || !drBr)
+  double2* drAB = dalloc<double2>(s, rslots);
+  if (!dcol || !dA || !dB || !drcol || !drAB)
     return fail(ASI_ENOMEM, "device allocation failed (neighbour tables)");
   // rows of a partial last slice stay padded
   HIPCHK(hipMemsetAsync(dcol, 0xff, 4 * slots, s->stream), s);
@@ -411,12 +412,11 @@ asi_status create_impl(const asi_params* p, const asi_device* dev, asi_sim* s) {
   HIPCHK(hipMemsetAsync(dB, 0, 8 * slots, s->stream), s);
   if (D == 0) {
     HIPCHK(hipMemsetAsync(drcol, 0xff, 4 * rslots, s->stream), s);
-    HIPCHK(hipMemsetAsync(drA, 0, 8 * rslots, s->stream), s);
-    HIPCHK(hipMemsetAsync(drBr, 0, 8 * rslots, s->stream), s);
+    HIPCHK(hipMemsetAsync(drAB, 0, 16 * rslots, s->stream), s);
   }
   if (D > 0)
     launch_neighbour_fill(dx, dy, dmx, dmy, dcx, dcy, dcs, dcm, n, gx, gy, cut2, p->alpha, D, dcol,
-                          dA, dB, drcol, drA, drBr, s->stream);
+                          dA, dB, drcol, drAB, s->stream);
   HIPCHK(hipStreamSynchronize(s->stream), s);
   s->mem.release(dcx);
   s->mem.release(dcy);
@@ -442,11 +442,17 @@ asi_status create_impl(const asi_params* p, const asi_device* dev, asi_sim* s) {
   I.A = dA;
   I.B = dB;
   I.rcol = drcol;
-  I.rA = drA;
-  I.rBr = drBr;
+  I.rAB = drAB;
   I.mx = dmx;
   I.my = dmy;
   I.hk = dhk;
+  I.ghk = nullptr;
+  if (n <= kLdsMaxN) {
+    double* g = dalloc<double>(s, n);
+    if (!g) return fail(ASI_ENOMEM, "device allocation failed (state)");
+    launch_inverse_hk(dhk, n, p->b, g, s->stream);
+    I.ghk = g;
+  }
   I.b = p->b;
   I.c = p->c;
   I.e_par = 2.0 / p->gamma;
@@ -492,7 +498,7 @@ asi_status create_impl(const asi_params* p, const asi_device* dev, asi_sim* s) {
   HIPCHK(hipMemsetAsync(I.ccount, 0, 4, s->stream), s);
   I.spec_min = kSpecMinDefault;
   if (const char* e = std::getenv("ASI_SPEC_MIN")) I.spec_min = std::atoll(e);
-  I.spec_switch = 2.5;
+  I.spec_switch = 0.0;
   if (const char* e = std::getenv("ASI_SPEC_SWITCH")) I.spec_switch = std::atof(e);
   // 16 wavefronts: the speculative relax spreads up to 2048 member and
   // neighbour slots over 1024 lanes; touched tiles are rescanned in parallel
@@ -1482,10 +1488,12 @@ struct Table {
   int64_t nblocks = 0;
   int32_t waves = 1;
   // Two groups of instances, relaxed side by side by kernels of their own:
-  // those on kPathLds and the others (kPathTree when none may speculate).
-  size_t lds_keys = 0, lds_other = 0;
-  bool any_keys = false, any_other = false;
-  RelaxPath other = kPathTree;
+  // those with their keys in LDS and the others.
+  struct Group {
+    bool any = false, spec = false;  // instances; whether one may speculate
+    size_t lds = 0;
+  };
+  Group keys, other;
   hipStream_t side = nullptr;  // the first group's launches, when there are both
   hipEvent_t fork = nullptr, join = nullptr;
   hipGraphExec_t exec = nullptr;
@@ -1541,24 +1549,20 @@ asi_status table_build(Table& T, std::vector<InstDev>& insts, const std::vector<
     int v = std::atoi(w);
     if (v >= 1 && v <= kMaxRelaxWaves) T.waves = v;
   }
-  T.lds_keys = T.lds_other = 0;
-  T.any_keys = T.any_other = false;
-  T.other = kPathTree;
+  T.keys = T.other = Table::Group{};
   for (int32_t k = 0; k < T.count; ++k) {
     InstDev& I = insts[k];
     if (I.n <= 0) continue;
     // the path depends on the launch's workgroup size
-    I.lds_keys = relax_keys_in_lds(I.n, I.D, T.waves, I.spec_min) ? 1 : 0;
-    if (I.lds_keys) {
-      T.any_keys = true;
-      T.lds_keys = std::max(T.lds_keys, relax_keys_lds_bytes(I.n, T.waves));
-    } else {
-      T.any_other = true;
-      T.lds_other = std::max(T.lds_other, relax_lds_bytes(I.n, I.l1_shift));
-      if (relax_may_speculate(I.D, T.waves)) T.other = kPathSpec;
-    }
+    I.lds_keys = relax_keys_in_lds(I, T.waves) ? 1 : 0;
+    const bool spec = relax_may_speculate(I.D, T.waves);
+    Table::Group& g = I.lds_keys ? T.keys : T.other;
+    g.any = true;
+    g.spec |= spec;
+    g.lds = std::max(g.lds, I.lds_keys ? relax_keys_lds_bytes(I.n, T.waves, spec)
+                                       : relax_lds_bytes(I.n, I.l1_shift));
   }
-  if (T.any_keys && T.any_other && !T.open_side())
+  if (T.keys.any && T.other.any && !T.open_side())
     return fail(ASI_EDEVICE, "stream creation failed (batch)");
   T.nblocks = (int64_t)bi.size();
   T.dI = static_cast<InstDev*>(T.mem.alloc(sizeof(InstDev) * std::max(1, T.count)));
@@ -1585,13 +1589,13 @@ asi_status table_build(Table& T, std::vector<InstDev>& insts, const std::vector<
 // both, the groups run side by side between st's earlier and later work.
 template <class F>
 void table_groups(Table& T, hipStream_t st, F launch) {
-  const bool both = T.any_keys && T.any_other;
+  const bool both = T.keys.any && T.other.any;
   if (both) {
     (void)hipEventRecord(T.fork, st);
     (void)hipStreamWaitEvent(T.side, T.fork, 0);
   }
-  if (T.any_keys) launch(kPathLds, T.lds_keys, both ? T.side : st);
-  if (T.any_other) launch(T.other, T.lds_other, st);
+  if (T.keys.any) launch(relax_path(true, T.keys.spec), T.keys.lds, both ? T.side : st);
+  if (T.other.any) launch(relax_path(false, T.other.spec), T.other.lds, st);
   if (both) {
     (void)hipEventRecord(T.join, T.side);
     (void)hipStreamWaitEvent(st, T.join, 0);
