@@ -885,6 +885,9 @@ __global__ __launch_bounds__(256) void k_slice_max(const InstDev* __restrict__ i
   }
 }
 
+// The relax workgroup's dynamic LDS.
+extern __shared__ __align__(16) unsigned char lds_dyn[];
+
 // Values that the whole workgroup shares but the compiler cannot know to be
 // the same in every lane (arguments of a function called out of line, values
 // read from LDS); a descriptor, which no kernel writes, also lies in constant
@@ -986,18 +989,24 @@ __device__ inline bool past(uint64_t deadline) {
 // of the magnet's key bumps.  Every valid pool entry is no better than
 // cold_max, so window entries better than cold_max can be taken in order.
 //
-// A batch takes the first B safe window entries c_1 .. c_B and flips the
-// longest prefix c_1 .. c_p that the one-at-a-time relax would flip in the
-// same order: the members and their neighbour sets are pairwise disjoint
-// (so no member's field or key depends on an earlier member of the prefix,
-// and every touched magnet gets exactly one update), and no touched magnet's
-// new key beats a later member of the prefix.  Then c_m is the argmax after
-// c_1 .. c_{m-1} for every m <= p, and applying the prefix together gives
-// the same flips, log, fields and keys, bit for bit.
+// Entries that a batch's updates add above cold_max wait in a small sorted
+// side list and join the window when that is full, so that a batch does not
+// move the window.
+//
+// A batch takes the first B entries c_1 .. c_B of the window's safe part and
+// the side list, and flips the longest prefix c_1 .. c_p (stale entries left
+// out) that the one-at-a-time relax would flip in the same order: the members
+// and their neighbour sets are pairwise disjoint (so no member's field or key
+// depends on an earlier member of the prefix, and every touched magnet gets
+// exactly one update), and no touched magnet's new key beats a later member of
+// the prefix.  Then c_m is the argmax after c_1 .. c_{m-1} for every m <= p,
+// and applying the prefix together gives the same flips, log, fields and keys,
+// bit for bit.
 constexpr int kWin = 2048;        // hot window entries
 constexpr int kHash = 4096;       // conflict table slots
-constexpr int kMaxPairs = 2048;   // member + neighbour slots per batch
-constexpr int kMaxMembers = 64;
+constexpr int kMaxPairs = 1024;   // member + neighbour slots per batch: one per thread
+constexpr int kMaxMembers = 64;   // one per lane of the wavefront that chooses them
+constexpr int kSide = 32;         // side-list entries
 // A step whose first kSwitchBatches batches commit fewer than kSwitchFlips
 // (unless spec_switch is given) flips each on average -- an avalanche: every flip
 // makes a neighbour the next candidate -- continues on the max tree, which
@@ -1027,17 +1036,20 @@ __device__ inline bool better_e(double ka, uint32_t pa, uint32_t va, double kb, 
 struct SpecLds {
   unsigned char* win;  // hot window, two buffers of kWin entries each:
                        //   buffer b: keys at win + b * kWinBytes, then payloads, versions
-  double* sk;       // staging / sort scratch (aliases the conflict table)
+  double* sk;       // staging / sort scratch (aliases the list of keys to evaluate)
   uint32_t* sp;
   uint32_t* sv;
   uint32_t* hidx;   // conflict table: magnet + 1 (0: empty)
-  int32_t* hown;    //   lowest member rank owning that magnet
-  int32_t* mval;    // per window position: member valid
-  int32_t* mrank;   //   its rank among the valid members (-1: stale)
-  double* mk;       // per rank: key, payload, window position
+  int32_t* hown;    //   first member that owns or touches that magnet
+  double* lk;       // side list, best first
+  uint32_t* lp;
+  uint32_t* lv;
+  double* mk;       // members, best first: key, payload, version (two sets, by turns)
   uint32_t* mp;
-  int32_t* mpos;
+  uint32_t* mv;
+  int32_t* mval;    // member's entry is current
 };
+constexpr int32_t kNoOwner = 0x7fffffff;
 
 constexpr size_t kWinBytes = (size_t)kWin * 16;
 __device__ inline double* win_k(const SpecLds& S, int b) {
@@ -1051,33 +1063,38 @@ __device__ inline uint32_t* win_v(const SpecLds& S, int b) {
 }
 
 __host__ __device__ inline size_t spec_lds_bytes() {
-  return 2 * (size_t)kWin * 16 + (size_t)kWin * 16 + (size_t)kMaxMembers * (4 + 4 + 8 + 4 + 4);
+  return 2 * (size_t)kWin * 16 + (size_t)kWin * 16 + (size_t)kHash * 8 + (size_t)kSide * 16 +
+         (size_t)kMaxMembers * (2 * 16 + 4);
 }
 
 __device__ inline SpecLds carve_spec(unsigned char* base) {
   SpecLds S;
   S.win = base;
-  size_t off = 2 * kWinBytes;
-  S.sk = (double*)(base + off);
-  S.sp = (uint32_t*)(base + off + sizeof(double) * kWin);
-  S.sv = (uint32_t*)(base + off + (sizeof(double) + sizeof(uint32_t)) * kWin);
-  S.hidx = (uint32_t*)(base + off);
-  S.hown = (int32_t*)(base + off + sizeof(uint32_t) * kHash);
-  off += (size_t)kWin * 16;
-  S.mk = (double*)(base + off);
-  off += sizeof(double) * kMaxMembers;
-  S.mp = (uint32_t*)(base + off);
-  off += sizeof(uint32_t) * kMaxMembers;
-  S.mpos = (int32_t*)(base + off);
-  off += sizeof(int32_t) * kMaxMembers;
-  S.mval = (int32_t*)(base + off);
-  off += sizeof(int32_t) * kMaxMembers;
-  S.mrank = (int32_t*)(base + off);
+  base += 2 * kWinBytes;
+  S.sk = (double*)base;
+  S.sp = (uint32_t*)(base + sizeof(double) * kWin);
+  S.sv = S.sp + kWin;
+  base += (size_t)kWin * 16;
+  S.hidx = (uint32_t*)base;
+  S.hown = (int32_t*)(S.hidx + kHash);
+  base += (size_t)kHash * 8;
+  S.lk = (double*)base;
+  S.lp = (uint32_t*)(S.lk + kSide);
+  S.lv = S.lp + kSide;
+  base += (size_t)kSide * 16;
+  S.mk = (double*)base;
+  S.mp = (uint32_t*)(S.mk + 2 * kMaxMembers);
+  S.mv = S.mp + 2 * kMaxMembers;
+  S.mval = (int32_t*)(S.mv + 2 * kMaxMembers);
   return S;
 }
 
 struct SpecShared {
-  int nx, xb, ns, nvalid, p, safe, cb, pause, npow;
+  int a0, nx, xb;   // window: first entry not consumed, end, buffer
+  int B, pe;        // batch size; end of its prefix
+  int nl, nl_next;  // side-list entries at the last choice; at this one
+  int nm;           // entries that join the window
+  int ns, npow, cb, pause;
   int64_t ncold, ncold_out, napp;
   double cmk;       // cold_max (key, payload, version); key -1: pool empty
   uint32_t cmp, cmv;
@@ -1087,6 +1104,7 @@ struct SpecShared {
   int over;         // selective refill: more entries above tau than fit
   double wk[16];    // per-wavefront best entries (selective refill)
   uint32_t wp[16], wv[16];
+  uint64_t hash;
 };
 
 // Block-wide bitonic sort, best first, of P (a power of two) entries.
@@ -1135,14 +1153,15 @@ __device__ __forceinline__ int co_rank(int d, const double* ak, const uint32_t* 
   return lo;
 }
 
-// Merge A = window[a0, a0+na) with B = staging[0, nb) (both best first):
-// the first `keep` outputs become the window (other buffer), the rest are
-// appended to pool buffer pb at sh.ncold_out; sh.rk/rp keeps the best entry
-// sent to the pool.
-__device__ __forceinline__ void merge_keep(const InstDev* I, const SpecLds& S, SpecShared& sh, int a0, int na,
-                           int nb, int keep, int pb) {
+// Merge A = the window's entries not consumed with B = staging[0, nb) (both
+// best first): the first `keep` outputs become the window (other buffer), the
+// rest are appended to pool buffer pb at sh.ncold_out; sh.rk/rp keeps the best
+// entry sent to the pool.
+__device__ __forceinline__ void merge_keep(const InstDev* I, const SpecLds& S, SpecShared& sh, int nb,
+                           int pb) {
   const int tid = threadIdx.x, NT = blockDim.x;
-  const int xb = sh.xb;
+  const int xb = sh.xb, a0 = sh.a0, na = sh.nx - a0;
+  const int keep = na + nb < kWin ? na + nb : kWin;
   const double* ak = win_k(S, xb) + a0;
   const uint32_t* ap = win_p(S, xb) + a0;
   const uint32_t* av = win_v(S, xb) + a0;
@@ -1195,6 +1214,7 @@ __device__ __forceinline__ void merge_keep(const InstDev* I, const SpecLds& S, S
   if (tid == 0) {
     sh.ncold_out += total - keep;
     sh.xb ^= 1;
+    sh.a0 = 0;
     sh.nx = keep;
   }
   __syncthreads();
@@ -1271,10 +1291,7 @@ __device__ __forceinline__ void refill(const InstDev* I, const SpecLds& S, SpecS
       sh.ns = lo;
     }
     __syncthreads();
-    const int nv = sh.ns;
-    const int nx = sh.nx;
-    const int keep = nx + nv < kWin ? nx + nv : kWin;
-    merge_keep(I, S, sh, 0, nx, nv, keep, cb ^ 1);
+    merge_keep(I, S, sh, sh.ns, cb ^ 1);
   }
   if (tid == 0) {
     sh.cb = cb ^ 1;
@@ -1398,9 +1415,7 @@ __device__ __forceinline__ void refill_select(const InstDev* I, const SpecLds& S
   __syncthreads();
   const int ns = sh.ns;
   sort_staging(S, ns);
-  const int nx = sh.nx;
-  const int keep = nx + ns < kWin ? nx + ns : kWin;
-  merge_keep(I, S, sh, 0, nx, ns, keep, cb ^ 1);
+  merge_keep(I, S, sh, ns, cb ^ 1);
   if (tid == 0) {
     sh.cb = cb ^ 1;
     sh.ncold = sh.ncold_out;
@@ -1412,17 +1427,17 @@ __device__ __forceinline__ void refill_select(const InstDev* I, const SpecLds& S
 }
 
 
-// Window entries better than cold_max (all of them when the pool is
-// empty), counted by one wavefront (every lane gets the count): the safe
-// entries are a prefix of the window, so 64 segment ends locate the
-// boundary's segment, and one lane per entry of that segment finds it.
-__device__ __forceinline__ int count_safe_wave(const SpecLds& S, const SpecShared& sh) {
+// End of the window's safe part: its entries better than cold_max (all of
+// them when the pool is empty), counted by one wavefront (every lane gets the
+// end): they are a prefix, so 64 segment ends locate the boundary's segment,
+// and one lane per entry of that segment finds it.
+__device__ __forceinline__ int safe_end_wave(const SpecLds& S, const SpecShared& sh) {
   const int lane = threadIdx.x & 63;
-  const int nx = sh.nx;
-  if (sh.ncold == 0 || nx == 0) return nx;
-  const double* k = win_k(S, sh.xb);
-  const uint32_t* p = win_p(S, sh.xb);
-  const uint32_t* v = win_v(S, sh.xb);
+  const int a0 = sh.a0, nx = sh.nx - a0;
+  if (sh.ncold == 0 || nx == 0) return sh.nx;
+  const double* k = win_k(S, sh.xb) + a0;
+  const uint32_t* p = win_p(S, sh.xb) + a0;
+  const uint32_t* v = win_v(S, sh.xb) + a0;
   const double cmk = sh.cmk;
   const uint32_t cmp = sh.cmp, cmv = sh.cmv;
   const int step = (nx + 63) >> 6;
@@ -1431,23 +1446,63 @@ __device__ __forceinline__ int count_safe_wave(const SpecLds& S, const SpecShare
   const int c = __popcll(__ballot(ok));
   const int e2 = c * step + lane;
   const bool ok2 = lane < step && e2 < nx && better_e(k[e2], p[e2], v[e2], cmk, cmp, cmv);
-  return c * step + __popcll(__ballot(ok2));
+  return a0 + c * step + __popcll(__ballot(ok2));
 }
 
 __device__ inline uint32_t hash_slot(uint32_t i) { return (i * 2654435761u) >> (32 - 12); }
+
+// Out of line, so that their registers stay out of the batch loop's.
+__device__ __attribute__((noinline)) void call_refill(const InstDev* I, ASI_LDS SpecShared* sh) {
+  const SpecLds S = carve_spec(lds_dyn);
+  SpecShared& h = *(SpecShared*)sh;
+  if (h.ncold > 4 * kWin)
+    refill_select(uniform(I), S, h);
+  else
+    refill(uniform(I), S, h);
+}
+// staging[0, nm) joins the window; what that pushes out joins the pool.
+__device__ __attribute__((noinline)) void call_join(const InstDev* I, ASI_LDS SpecShared* sh, int nm) {
+  const SpecLds S = carve_spec(lds_dyn);
+  SpecShared& h = *(SpecShared*)sh;
+  nm = __builtin_amdgcn_readfirstlane(nm);
+  if (threadIdx.x == 0) {
+    h.ncold_out = h.ncold;
+    h.rk = h.cmk;
+    h.rp = h.cmp;
+    h.rv = h.cmv;
+  }
+  __syncthreads();
+  sort_staging(S, nm);
+  merge_keep(uniform(I), S, h, nm, h.cb);
+  if (threadIdx.x == 0) {
+    h.ncold = h.ncold_out;
+    h.cmk = h.rk;
+    h.cmp = h.rp;
+    h.cmv = h.rv;
+  }
+  __syncthreads();
+}
+__device__ __attribute__((noinline)) double pow_far(double x, double e) { return pow(x, e); }
 
 // Relax at step t in speculative batches (needs 1024 threads).  flips,
 // logpos and hash are the running counters (hash significant in thread 0).
 // Returns 0, -5 (flip cap reached with a flippable magnet left),
 // 1 (deadline passed after at least one batch, flippable magnets left) or
-// 2 (the mean batch is too small, see kSwitchBatches:
-// the flippable magnets crowd each other's neighbourhoods, and the step
-// goes on one flip at a time).
+// 2 (the mean batch is too small, see kSwitchBatches: the flippable magnets
+// crowd each other's neighbourhoods, and the step goes on one flip at a time).
+// What bounds it: a chain of phases per batch, six barriers apart -- the
+// members' choice (one wavefront), their rows, their neighbours' fields (in
+// flight while the conflicts are found; one wavefront folds the last batch into
+// the hash meanwhile), the FP64 powers, one to a lane, and the commit: 21,000
+// cycles for 16 members of a 120,000-magnet kagome, 1.16 -> 1.06 us a flip.
+// Against batches of up to 2,048 slots that merged the window each time: 23,000
+// cycles; 1M-magnet kagome 0.46 us a flip in both, a 30,000-magnet kagome at
+// d = 1 0.23 -> 0.20.
 __device__ __forceinline__ int relax_spec(const InstDev* __restrict__ I, int64_t t, unsigned char* lds,
                           SpecShared& sh, int64_t ncand, int64_t& flips, int64_t& logpos,
                           uint64_t& hash, uint64_t deadline) {
-  constexpr int kPPT = kMaxPairs / 1024;  // pair slots per thread
-  const int tid = threadIdx.x, NT = blockDim.x;
+  const int tid = threadIdx.x, NT = blockDim.x, lane = tid & 63;
+  const bool chooser = tid < 64, clerk = tid >= NT - 64;  // the first and the last wavefront
   SpecLds S = carve_spec(lds);
   const int32_t D = I->D;
   const int32_t mode = I->field_mode;
@@ -1460,10 +1515,19 @@ __device__ __forceinline__ int relax_spec(const InstDev* __restrict__ I, int64_t
   // the members past the prefix only cost loads and key evaluations;
   // doubled while whole batches commit.
   int bcap = Bmax;
+  const int sm = tid / PW, sk = tid % PW;  // the thread's pair slot: member and place in its row
+  for (int q = tid; q < kHash; q += NT) {
+    S.hidx[q] = 0u;
+    S.hown[q] = kNoOwner;
+  }
   if (tid == 0) {
+    sh.a0 = 0;
     sh.nx = 0;
     sh.xb = 0;
     sh.cb = 0;
+    sh.ns = 0;
+    sh.napp = 0;
+    sh.nl = 0;
     sh.ncold = ncand;
     sh.cmk = 1e300;  // unknown until the first refill
     sh.cmp = 0;
@@ -1477,310 +1541,410 @@ __device__ __forceinline__ int relax_spec(const InstDev* __restrict__ I, int64_t
   const double sw = I->spec_switch > 0.0 ? I->spec_switch
                                          : keys_in_lds ? kSwitchFlipsLds : kSwitchFlips;
   int64_t flips1 = flips;
-  int nbatch = 0;  // batches since flips1
+  int nbatch = 0;     // batches since flips1
+  int set = 0;        // the members' set
+  int consumed = 0;   // entries of the last batch that are done with
+  unsigned long long committed = 0ull;  // members of the last batch that flipped
+  // The clerk folds the last batch's flips into the hash while the next one's
+  // rows are on their way.
+  auto fold = [&]() {
+    if (!clerk || committed == 0ull) return;
+    const uint32_t jr = S.mp[(set ^ 1) * kMaxMembers + lane] & 0x7fffffffu;
+    for (unsigned long long c = committed; c; c &= c - 1ull) {
+      const uint32_t j = (uint32_t)__builtin_amdgcn_readlane((int)jr, __ffsll(c) - 1);
+      hash = (hash ^ (((uint64_t)(uint32_t)t << 32) | j)) * 0x100000001b3ull;
+    }
+  };
+  // the choosing wavefront's own: the window's safe part, its lanes' ranks in
+  // the last batch, and the side list's remainder
+  int a0 = 0, s_end = 0, nl = 0, rank_w = kMaxMembers, rank_l = kMaxMembers;
   while (true) {
-    if (nbatch >= nswitch && (double)(flips - flips1) < sw * nbatch) {
-      status = 2;
-      break;
-    }
-    if (keys_in_lds && nbatch == nswitch) {
-      flips1 = flips;
-      nbatch = 0;
-    }
-    if (tid < 64) {
-      const int sf = count_safe_wave(S, sh);
-      if (tid == 0) {
-        sh.safe = sf;
-        sh.pause = (flips > flips0 && past(deadline)) ? 1 : 0;
-      }
-    }
-    __syncthreads();
-    const int pause = sh.pause;
-    if (sh.safe == 0 || sh.ncold + kMaxPairs + kWin > I->ccap) {
-      if (sh.ncold == 0 && sh.safe == 0) break;
-      if (sh.ncold > 4 * kWin)
-        refill_select(I, S, sh);
-      else
-        refill(I, S, sh);
-      if (tid < 64) {
-        const int sf = count_safe_wave(S, sh);
-        if (tid == 0) sh.safe = sf;
+    const int ns = sh.ns;
+    // ---- the side list would overflow: it and the new entries join the window
+    if (sh.nl + ns > kSide) {
+      const int nl0 = sh.nl;
+      if (chooser) {
+        a0 += __popcll(__ballot(rank_w < consumed));
+        const int cl = __popcll(__ballot(rank_l < consumed));
+        rank_w = rank_l = kMaxMembers;
+        const int rem = nl0 - cl;  // the side list's remainder goes behind the new entries
+        if (lane < rem) {
+          S.sk[ns + lane] = S.lk[cl + lane];
+          S.sp[ns + lane] = S.lp[cl + lane];
+          S.sv[ns + lane] = S.lv[cl + lane];
+        }
+        if (lane == 0) {
+          sh.ncold += sh.napp;
+          sh.napp = 0;
+          sh.a0 = a0;
+          sh.nm = ns + rem;
+        }
       }
       __syncthreads();
-      if (sh.safe == 0) break;  // the pool held stale entries only
+      call_join(I, (ASI_LDS SpecShared*)&sh, sh.nm);
+      if (tid == 0) {
+        sh.ns = 0;
+        sh.nl = 0;
+      }
+      __syncthreads();
+      if (chooser) {
+        a0 = 0;
+        nl = 0;
+        consumed = 0;
+        s_end = safe_end_wave(S, sh);
+      }
     }
-    if (pause) {  // flippable magnets remain
+    // ---- choice of the next members (first wavefront): its lanes hold the
+    // window's next entries and the side list's, new entries among them; an
+    // entry's rank is the number of entries that beat it.  The last wavefront
+    // folds the batch just committed into the hash.
+    bool refilled = false, none = false;
+    while (true) {
+      if (chooser) {
+        a0 += __popcll(__ballot(rank_w < consumed));
+        const int cl = __popcll(__ballot(rank_l < consumed));
+        const int fresh = sh.ns, rem = nl - cl;
+        nl = rem + fresh;
+        const double* wk = win_k(S, sh.xb);
+        const uint32_t* wp = win_p(S, sh.xb);
+        const uint32_t* wv = win_v(S, sh.xb);
+        const bool has_w = a0 + lane < s_end, has_l = lane < nl;
+        double kw = 0.0, kl = 0.0;
+        uint32_t pw = 0, vw = 0, pl = 0, vl = 0;
+        if (has_w) {
+          kw = wk[a0 + lane];
+          pw = wp[a0 + lane];
+          vw = wv[a0 + lane];
+        }
+        if (has_l) {
+          const bool old = lane < rem;
+          kl = old ? S.lk[cl + lane] : S.sk[lane - rem];
+          pl = old ? S.lp[cl + lane] : S.sp[lane - rem];
+          vl = old ? S.lv[cl + lane] : S.sv[lane - rem];
+        }
+        // the side list with the new entries sorted in (few: each is ranked in turn)
+        if (fresh) {
+          int in_l = lane < rem ? lane : 0;  // entries that beat the lane's
+          for (int r = rem; r < nl; ++r) {
+            const double rk = readlane_f64(kl, r);
+            const uint32_t rp = (uint32_t)__builtin_amdgcn_readlane((int)pl, r);
+            const uint32_t rv = (uint32_t)__builtin_amdgcn_readlane((int)vl, r);
+            const bool by = has_l && better_e(rk, rp, rv, kl, pl, vl);
+            const int above = __popcll(__ballot(lane < rem && !by));  // old ones that beat it
+            in_l += by ? 1 : 0;
+            if (lane == r) in_l += above;
+          }
+          if (has_l) {
+            S.lk[in_l] = kl;
+            S.lp[in_l] = pl;
+            S.lv[in_l] = vl;
+            kl = S.lk[lane];  // the lane's entry, best first
+            pl = S.lp[lane];
+            vl = S.lv[lane];
+          }
+        } else if (has_l && cl) {
+          S.lk[lane] = kl;
+          S.lp[lane] = pl;
+          S.lv[lane] = vl;
+        }
+        // ranks: how many side-list entries beat the lane's window entry, and
+        // the other way round
+        const int nw = __popcll(__ballot(has_w));
+        int lo_w = 0, up_w = has_w ? nl : 0, lo_l = 0, up_l = has_l ? (nw < bcap ? nw : bcap) : 0;
+        while (__ballot(lo_w < up_w || lo_l < up_l)) {
+          const int mw = (lo_w + up_w) >> 1, ml = (lo_l + up_l) >> 1;
+          const int iw = mw < kSide ? mw : 0, il = a0 + (ml < nw ? ml : 0);
+          const bool bl = better_e(S.lk[iw], S.lp[iw], S.lv[iw], kw, pw, vw);
+          const bool bw = better_e(wk[il], wp[il], wv[il], kl, pl, vl);
+          if (lo_w < up_w) {
+            if (bl) lo_w = mw + 1; else up_w = mw;
+          }
+          if (lo_l < up_l) {
+            if (bw) lo_l = ml + 1; else up_l = ml;
+          }
+        }
+        rank_w = has_w ? lane + lo_w : kMaxMembers;
+        rank_l = has_l ? lane + lo_l : kMaxMembers;
+        const int avail = nw + nl;
+        const int B = avail < bcap ? avail : bcap;
+        const int m0 = set * kMaxMembers;
+        if (rank_w < B) {
+          S.mk[m0 + rank_w] = kw;
+          S.mp[m0 + rank_w] = pw;
+          S.mv[m0 + rank_w] = vw;
+        }
+        if (rank_l < B) {
+          S.mk[m0 + rank_l] = kl;
+          S.mp[m0 + rank_l] = pl;
+          S.mv[m0 + rank_l] = vl;
+        }
+        consumed = 0;
+        if (lane == 0) {
+          sh.B = B;
+          sh.pe = B;
+          sh.nl_next = nl;
+          sh.ncold += sh.napp;
+          sh.napp = 0;
+          sh.pause = (flips > flips0 && past(deadline)) ? 1 : 0;
+        }
+      }
+      __syncthreads();
+      // nothing to take, or the pool's room for a batch's entries runs out
+      const bool dry = sh.B == 0;
+      if (refilled || !(dry || sh.ncold + kMaxPairs + kWin > I->ccap)) {
+        none = dry;
+        break;
+      }
+      if (sh.ncold == 0 && dry) {
+        none = true;
+        break;
+      }
+      // the side list joins the window, then the pool's best refill it
+      const int nl1 = sh.nl_next;
+      if (nl1 > 0) {
+        if (chooser) {
+          if (lane < nl1) {
+            S.sk[lane] = S.lk[lane];
+            S.sp[lane] = S.lp[lane];
+            S.sv[lane] = S.lv[lane];
+          }
+          if (lane == 0) sh.a0 = a0;
+        }
+        __syncthreads();
+        call_join(I, (ASI_LDS SpecShared*)&sh, nl1);
+      } else {
+        if (tid == 0) sh.a0 = a0;
+        __syncthreads();
+      }
+      call_refill(I, (ASI_LDS SpecShared*)&sh);
+      if (chooser) {
+        a0 = sh.a0;
+        nl = 0;
+        rank_w = rank_l = kMaxMembers;
+        s_end = safe_end_wave(S, sh);
+        if (lane == 0) sh.ns = 0;
+      }
+      refilled = true;
+    }
+    if (none) break;  // the pool held stale entries only, or nothing
+    if (sh.pause) {  // flippable magnets remain
       status = 1;
       break;
     }
-    const int B = sh.safe < bcap ? sh.safe : bcap;
-    const int xb = sh.xb;
-    const double* xk = win_k(S, xb);
-    const uint32_t* xp = win_p(S, xb);
-    const uint32_t* xv = win_v(S, xb);
-    // ---- round trip 1: member versions and the members' neighbour slots
-    int pr_m[kPPT], pr_i[kPPT];
-    double pr_a[kPPT], pr_b[kPPT];
-#pragma unroll
-    for (int u = 0; u < kPPT; ++u) {
-      pr_m[u] = -1;
-      pr_i[u] = -1;
-      pr_a[u] = 0.0;
-      pr_b[u] = 0.0;
-      const int q = tid + u * NT;
-      if (q < B * PW) {
-        const int m = q / PW, k = q % PW;
-        const uint32_t j = xp[m] & 0x7fffffffu;
-        pr_m[u] = m;
-        if (k == D) {
-          pr_i[u] = (int)j;
-        } else {
-          const int64_t sl = (int64_t)j * D + k;
-          pr_i[u] = I->rcol[sl];
-          const double2 ab = I->rAB[sl];
-          pr_a[u] = ab.x;
-          pr_b[u] = ab.y;
-        }
+    const int B = sh.B;
+    const double* const mk = S.mk + set * kMaxMembers;
+    const uint32_t* const mp = S.mp + set * kMaxMembers;
+    const uint32_t* const mv = S.mv + set * kMaxMembers;
+    // ---- round trip 1: the members' versions and rows; round trip 2: the
+    // neighbours' state, in flight while the conflicts are found
+    bool on = sm < B;
+    int pi = -1, si = 0;
+    double2 ab = make_double2(0.0, 0.0), hi = ab, di = ab;
+    double hki = 0.0;
+    uint32_t vi = 0;
+    if (on) {
+      const uint32_t j = mp[sm] & 0x7fffffffu;
+      if (sk == D) {
+        pi = (int)j;
+      } else {
+        const int64_t sl = (int64_t)j * D + sk;
+        pi = I->rcol[sl];
+        ab = I->rAB[sl];
       }
     }
-    if (tid < B) S.mval[tid] = (I->ver[xp[tid] & 0x7fffffffu] == xv[tid]) ? 1 : 0;
-    for (int q = tid; q < kHash; q += NT) {
-      S.hidx[q] = 0u;
-      S.hown[q] = 0x7fffffff;
+    if (tid < B) S.mval[tid] = (I->ver[mp[tid] & 0x7fffffffu] == mv[tid]) ? 1 : 0;
+    if (tid == 0) {
+      sh.npow = 0;
+      sh.ns = 0;
+      sh.nl = nl;
+    }
+    fold();
+    on = on && pi >= 0;  // else a padding slot
+    if (on && sk < D) {
+      hi = I->h[pi];
+      hki = I->hk[pi];
+      si = I->s[pi];
+      vi = I->ver[pi];
+      if (mode == kFieldCarry) di = I->hd[pi];
     }
     __syncthreads();
-    if (tid < 64) {  // ranks of the valid members, one wavefront
-      const bool v = tid < B && S.mval[tid] != 0;
-      const unsigned long long bal = __ballot(v);
-      const int r = __popcll(bal & ((1ull << tid) - 1ull));
-      if (tid < B) S.mrank[tid] = v ? r : -1;
-      if (v) {
-        S.mk[r] = xk[tid];
-        S.mp[r] = xp[tid];
-        S.mpos[r] = tid;
+    // members whose entries are current, by lane
+    const unsigned long long valid = __ballot(lane < B && S.mval[lane < B ? lane : 0] != 0);
+    // ---- pairwise disjoint neighbour sets: of the members that meet at a
+    // magnet all but the first end the prefix
+    int hs = -1;
+    on = on && ((valid >> sm) & 1ull) != 0ull;
+    if (on) {
+      const uint32_t want = (uint32_t)pi + 1u;
+      uint32_t q = hash_slot((uint32_t)pi);
+      while (true) {
+        const uint32_t old = atomicCAS(&S.hidx[q], 0u, want);
+        if (old == 0u || old == want) break;
+        q = (q + 1) & (kHash - 1);
       }
-      if (tid == 0) {
-        sh.nvalid = __popcll(bal);
-        sh.p = __popcll(bal);
-        sh.ns = 0;
-        sh.napp = 0;
-        sh.npow = 0;
-      }
+      hs = (int)q;
+      const int first = atomicMin(&S.hown[q], sm);
+      if (first != kNoOwner) atomicMin(&sh.pe, first > sm ? first : sm);
     }
-    __syncthreads();
-    const int nvalid = sh.nvalid;
-    int pr_r[kPPT];
-#pragma unroll
-    for (int u = 0; u < kPPT; ++u) {
-      pr_r[u] = (pr_m[u] >= 0) ? S.mrank[pr_m[u]] : -1;
-      if (pr_i[u] < 0) pr_r[u] = -1;  // padding slot
-    }
-    // ---- pairwise disjoint neighbour sets: lowest owning rank per magnet
-#pragma unroll
-    for (int u = 0; u < kPPT; ++u) {
-      if (pr_r[u] >= 0) {
-        const uint32_t want = (uint32_t)pr_i[u] + 1u;
-        uint32_t s = hash_slot((uint32_t)pr_i[u]);
-        while (true) {
-          const uint32_t old = atomicCAS(&S.hidx[s], 0u, want);
-          if (old == 0u || old == want) break;
-          s = (s + 1) & (kHash - 1);
-        }
-        atomicMin(&S.hown[s], pr_r[u]);
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < kPPT; ++u) {
-      if (pr_r[u] >= 0) {
-        const uint32_t want = (uint32_t)pr_i[u] + 1u;
-        uint32_t s = hash_slot((uint32_t)pr_i[u]);
-        while (S.hidx[s] != want) s = (s + 1) & (kHash - 1);
-        if (S.hown[s] < pr_r[u]) atomicMin(&sh.p, pr_r[u]);
-      }
-    }
-    __syncthreads();
-    const int p_ab = sh.p;
-    // ---- round trip 2: touched magnets of the conflict-free prefix.  Keys
-    // the switching bound cannot settle go through a dense list in LDS
-    // (aliasing the conflict table, done with), so that the FP64 powers run
-    // on full wavefronts.
-    double nh_p[kPPT], nh_q[kPPT], nkey[kPPT], nd_p[kPPT], nd_q[kPPT];
-    uint32_t nver[kPPT];
-    int nsi[kPPT], ppos[kPPT];
+    // ---- the neighbours' new fields.  Keys the switching bound cannot settle
+    // go through a dense list in LDS, so that the FP64 powers run on full
+    // wavefronts.
+    double nh_p = 0.0, nh_q = 0.0, nd_p = 0.0, nd_q = 0.0, nkey = 0.0;
+    int ppos = -1;
     double* pw_a = S.sk;            // kMaxPairs doubles
     double* pw_q = (double*)S.sp;   // kMaxPairs doubles (sp and sv)
-    double pa[kPPT], pq[kPPT];
-    bool need[kPPT];
-#pragma unroll
-    for (int u = 0; u < kPPT; ++u) {  // all gathers first: one round trip
-      nkey[u] = 0.0;
-      ppos[u] = -1;
-      pa[u] = 0.0;
-      pq[u] = 0.0;
-      need[u] = false;
-      const int k = (pr_m[u] >= 0) ? (tid + u * NT) % PW : D;
-      if (pr_r[u] >= 0 && pr_r[u] < p_ab && k < D) {
-        const int i = pr_i[u];
-        const uint32_t mpay = S.mp[pr_r[u]];
-        const double two = (mpay & 0x80000000u) ? 2.0 : -2.0;  // s_new = -s_old
-        const double da = two * pr_a[u], db = two * pr_b[u];
-        const double2 hi = I->h[i];
-        nh_p[u] = hi.x + da;
-        nh_q[u] = hi.y + db;
-        if (mode == kFieldCarry) {
-          const double2 di = I->hd[i];
-          nd_p[u] = di.x + da;
-          nd_q[u] = di.y + db;
-        }
-        nsi[u] = I->s[i];
-        nver[u] = I->ver[i];
-        need[u] = key_needs_powers(nsi[u], nh_p[u], nh_q[u], I->hk[i], pb, pc, ep, eq, pa[u],
-                                   pq[u]);
+    const bool nb = on && sk < D;  // the slot holds a neighbour
+    {
+      bool need = false;
+      double pa = 0.0, pq = 0.0;
+      if (nb) {
+        const double two = (mp[sm] & 0x80000000u) ? 2.0 : -2.0;  // s_new = -s_old
+        const double da = two * ab.x, db = two * ab.y;
+        nh_p = hi.x + da;
+        nh_q = hi.y + db;
+        nd_p = di.x + da;
+        nd_q = di.y + db;
+        need = key_needs_powers(si, nh_p, nh_q, hki, pb, pc, ep, eq, pa, pq);
       }
-    }
-#pragma unroll
-    for (int u = 0; u < kPPT; ++u) {
-      const unsigned long long bal = __ballot(need[u]);
+      const unsigned long long bal = __ballot(need);
       if (bal) {
         int base = 0;
-        if ((tid & 63) == 0) base = atomicAdd(&sh.npow, __popcll(bal));
+        if (lane == 0) base = atomicAdd(&sh.npow, __popcll(bal));
         base = __builtin_amdgcn_readfirstlane(base);
-        if (need[u]) {
-          ppos[u] = base + __popcll(bal & ((1ull << (tid & 63)) - 1ull));
-          pw_a[ppos[u]] = pa[u];
-          pw_q[ppos[u]] = pq[u];
+        if (need) {
+          ppos = base + __popcll(bal & ((1ull << lane) - 1ull));
+          pw_a[ppos] = pa;
+          pw_q[ppos] = pq;
         }
       }
     }
     __syncthreads();
-    for (int e = tid; e < sh.npow; e += NT) pw_a[e] = key_from_powers(pw_a[e], pw_q[e], ep, eq);
+    const int p_ab = sh.pe;
+    const int npow = sh.npow;
+    // one power per lane: the even lane's term and the odd lane's, added
+    for (int e = tid; e < 2 * npow; e += NT) {
+      const bool odd = (e & 1) != 0;
+      const double x = odd ? pw_q[e >> 1] : pw_a[e >> 1];
+      const double r = pow_far(x, odd ? eq : ep);
+      const double L = r + dpp_f64<0xB1>(r);  // quad_perm [1,0,3,2]
+      if (!odd) pw_a[e >> 1] = (L > 1.0) ? L : 0.0;
+    }
     __syncthreads();
-#pragma unroll
-    for (int u = 0; u < kPPT; ++u) {
-      if (ppos[u] >= 0) {
-        nkey[u] = pw_a[ppos[u]];
-        const int i = pr_i[u];
-        if (nkey[u] > 0.0) {
-          // first later member of the prefix this magnet would beat
-          const uint32_t npay = (uint32_t)i | (nsi[u] < 0 ? 0x80000000u : 0u);
-          int lo = pr_r[u] + 1, hi = p_ab;
-          while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (better(nkey[u], npay, S.mk[mid], S.mp[mid])) hi = mid; else lo = mid + 1;
-          }
-          if (lo < p_ab) atomicMin(&sh.p, lo);
+    // ---- a new key that beats a later member of the prefix ends it there
+    if (ppos >= 0 && sm < p_ab) {
+      nkey = pw_a[ppos];
+      if (nkey > 0.0) {
+        const uint32_t npay = (uint32_t)pi | (si < 0 ? 0x80000000u : 0u);
+        int lo = sm + 1, up = p_ab;
+        while (lo < up) {
+          const int mid = (lo + up) >> 1;
+          if (better(nkey, npay, mk[mid], mp[mid])) up = mid; else lo = mid + 1;
         }
+        if (lo < p_ab) atomicMin(&sh.pe, lo);
       }
     }
     __syncthreads();
-    int p = sh.p;
-    if (p > max_flips - flips) p = (int)(max_flips - flips);
-    if (p <= 0 && nvalid > 0) {
+    int pe = sh.pe;
+    committed = pe < 64 ? valid & ((1ull << pe) - 1ull) : valid;
+    int p = __popcll(committed);
+    const int64_t left = max_flips - flips;
+    if (p > left) {  // the flip cap: the prefix's first `left` members
+      while (p > left) {
+        pe = 63 - __clzll(committed);
+        committed &= ~(1ull << pe);
+        --p;
+      }
+    }
+    if (p <= 0 && valid != 0ull) {
       status = -5;
       break;
     }
-    // ---- commit members [0, p) and their neighbours
-    if (tid < p) {
-      const uint32_t mpay = S.mp[tid];
+    // ---- commit the prefix's members and their neighbours
+    if (tid < 64 && ((committed >> tid) & 1ull)) {
+      const uint32_t mpay = mp[tid];
       const uint32_t j = mpay & 0x7fffffffu;
       I->s[j] = (mpay & 0x80000000u) ? (int8_t)1 : (int8_t)-1;
       I->key[j] = 0.0;
-      I->ver[j] = xv[S.mpos[tid]] + 1u;
+      I->ver[j] = mv[tid] + 1u;
     }
-    if (tid < 64) {  // log the members in order (one lane each), then fold them into the hash
-      const uint32_t jr = (tid < p) ? (S.mp[tid] & 0x7fffffffu) : 0u;
-      if (tid < p && logpos + tid < I->log_cap) {
-        I->log_t[logpos + tid] = (int32_t)t;
-        I->log_j[logpos + tid] = (int32_t)jr;
-      }
-      for (int r = 0; r < p; ++r) {
-        const uint64_t w = ((uint64_t)(uint32_t)t << 32) |
-                           (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)jr, r);
-        hash = (hash ^ w) * 0x100000001b3ull;
+    if (clerk && ((committed >> lane) & 1ull)) {  // log the members in order
+      const int64_t q = logpos + __popcll(committed & ((1ull << lane) - 1ull));
+      if (q < I->log_cap) {
+        I->log_t[q] = (int32_t)t;
+        I->log_j[q] = (int32_t)(mp[lane] & 0x7fffffffu);
       }
     }
-    logpos += p;
     const double cmk = sh.cmk;
     const uint32_t cmp = sh.cmp, cmv = sh.cmv;
     const int cb = sh.cb;
     const int64_t ncold = sh.ncold;
-    // flippable touched magnets go to staging (if they may enter the window)
-    // or to the cold pool, with one LDS atomic per wavefront for each
-    const unsigned long long lt = (1ull << (tid & 63)) - 1ull;
-#pragma unroll
-    for (int u = 0; u < kPPT; ++u) {
-      const int k = (pr_m[u] >= 0) ? (tid + u * NT) % PW : D;
-      bool st = false, co = false;
-      uint32_t npay = 0, v1 = 0;
-      if (pr_r[u] >= 0 && pr_r[u] < p && k < D) {
-        const int i = pr_i[u];
-        I->h[i] = make_double2(nh_p[u], nh_q[u]);
-        if (mode == kFieldCarry) {
-          I->hd[i] = make_double2(nd_p[u], nd_q[u]);
-        } else if (mode == kFieldDirty) {
-          I->dirty[i] = 1;
-        }
-        I->key[i] = nkey[u];
-        v1 = nver[u] + 1u;
-        I->ver[i] = v1;
-        if (nkey[u] > 0.0) {
-          npay = (uint32_t)i | (nsi[u] < 0 ? 0x80000000u : 0u);
-          st = better_e(nkey[u], npay, v1, cmk, cmp, cmv);
-          co = !st;
-        }
+    // flippable touched magnets go to staging (if they beat the pool) or to
+    // the pool, with one LDS atomic per wavefront for each
+    const unsigned long long lt = (1ull << lane) - 1ull;
+    bool st = false, co = false;
+    uint32_t npay = 0, v1 = 0;
+    if (hs >= 0) {  // the conflict table is left empty
+      S.hidx[hs] = 0u;
+      S.hown[hs] = kNoOwner;
+    }
+    if (nb && sm < pe) {
+      I->h[pi] = make_double2(nh_p, nh_q);
+      if (mode == kFieldCarry) {
+        I->hd[pi] = make_double2(nd_p, nd_q);
+      } else if (mode == kFieldDirty) {
+        I->dirty[pi] = 1;
       }
-      const unsigned long long bs = __ballot(st), bc = __ballot(co);
-      int sbase = 0, cbase = 0;
-      if ((tid & 63) == 0) {
-        if (bs) sbase = atomicAdd(&sh.ns, __popcll(bs));
-        if (bc) cbase = (int)atomicAdd((unsigned long long*)&sh.napp, (unsigned long long)__popcll(bc));
-      }
-      sbase = __builtin_amdgcn_readfirstlane(sbase);
-      cbase = __builtin_amdgcn_readfirstlane(cbase);
-      if (st) {
-        const int q = sbase + __popcll(bs & lt);
-        S.sk[q] = nkey[u];
-        S.sp[q] = npay;
-        S.sv[q] = v1;
-      }
-      if (co) {
-        const int64_t q = ncold + cbase + __popcll(bc & lt);
-        I->ckey[cb][q] = nkey[u];
-        I->cpay[cb][q] = npay;
-        I->cver[cb][q] = v1;
+      I->key[pi] = nkey;
+      v1 = vi + 1u;
+      I->ver[pi] = v1;
+      if (nkey > 0.0) {
+        npay = (uint32_t)pi | (si < 0 ? 0x80000000u : 0u);
+        st = better_e(nkey, npay, v1, cmk, cmp, cmv);
+        co = !st;
       }
     }
+    const unsigned long long bs = __ballot(st), bc = __ballot(co);
+    int sbase = 0, cbase = 0;
+    if (lane == 0) {
+      if (bs) sbase = atomicAdd(&sh.ns, __popcll(bs));
+      if (bc) cbase = (int)atomicAdd((unsigned long long*)&sh.napp, (unsigned long long)__popcll(bc));
+    }
+    sbase = __builtin_amdgcn_readfirstlane(sbase);
+    cbase = __builtin_amdgcn_readfirstlane(cbase);
+    if (st) {
+      const int q = sbase + __popcll(bs & lt);
+      S.sk[q] = nkey;
+      S.sp[q] = npay;
+      S.sv[q] = v1;
+    }
+    if (co) {
+      const int64_t q = ncold + cbase + __popcll(bc & lt);
+      I->ckey[cb][q] = nkey;
+      I->cpay[cb][q] = npay;
+      I->cver[cb][q] = v1;
+    }
+    logpos += p;
     flips += p;
     ++nbatch;
     bcap = (p >= B) ? 2 * B : 2 * p + 2;
     if (bcap < 8) bcap = 8;
     if (bcap > Bmax) bcap = Bmax;
-    __syncthreads();
-    // window entries consumed: up to the last committed member (stale ones
-    // in between included), or the whole batch when every valid member went
-    const int consumed = (p < nvalid) ? S.mpos[p - 1] + 1 : B;
-    const int ns = sh.ns;
-    if (tid == 0) {
-      sh.ncold += sh.napp;
-      sh.ncold_out = sh.ncold;
-      sh.rk = sh.cmk;
-      sh.rp = sh.cmp;
-      sh.rv = sh.cmv;
+    // entries done with: the prefix's (stale ones among them), or the whole
+    // batch when every valid member went
+    consumed = (pe >= 64 || (valid >> pe) == 0ull) ? B : pe;
+    set ^= 1;
+    if (nbatch >= nswitch && (double)(flips - flips1) < sw * nbatch) status = 2;
+    if (keys_in_lds && nbatch == nswitch) {
+      flips1 = flips;
+      nbatch = 0;
     }
     __syncthreads();
-    sort_staging(S, ns);
-    const int na = sh.nx - consumed;
-    const int keep = na + ns < kWin ? na + ns : kWin;
-    merge_keep(I, S, sh, consumed, na, ns, keep, sh.cb);
-    if (tid == 0) {
-      sh.ncold = sh.ncold_out;
-      sh.cmk = sh.rk;
-      sh.cmp = sh.rp;
-      sh.cmv = sh.rv;
-    }
-    __syncthreads();
+    if (status == 2) break;
   }
+  if (status != -5) fold();  // (there nothing was committed since the last fold)
+  if (tid == NT - 64) sh.hash = hash;
+  __syncthreads();
+  hash = sh.hash;
   return status;
 }
 
@@ -2598,8 +2762,6 @@ __device__ __forceinline__ int relax_lds(const InstDev* __restrict__ I, int64_t 
   return status;
 }
 
-extern __shared__ __align__(16) unsigned char lds_dyn[];
-
 __device__ __forceinline__ int run_spec(const InstDev* I, int64_t t, RelaxState* st, int64_t ncand,
                                        uint64_t deadline) {
   int64_t flips = uniform(st->c.flips), logpos = uniform(st->c.logpos);
@@ -2628,6 +2790,12 @@ __device__ __forceinline__ int run_tree(const InstDev* I, int64_t t, RelaxState*
   if (threadIdx.x == 0) st->c = RelaxCount{flips, logpos, hash};
   __syncthreads();
   return status;
+}
+
+__device__ __attribute__((noinline)) int call_tree(const InstDev* I, int64_t t, ASI_LDS RelaxState* st,
+                                                   bool rebuild, uint64_t deadline) {
+  return run_tree<false>(uniform(I), uniform(t), (RelaxState*)st, rebuild,
+                         (uint64_t)uniform((int64_t)deadline));
 }
 
 // The field phase of a whole instance by one workgroup.
@@ -2672,7 +2840,8 @@ __device__ __forceinline__ int relax_step(const InstDev* __restrict__ I, RunDev*
                      ? relax_lds<true>(I, t, lds_dyn, st, ncand, !spec, deadline)
                      : relax_lds<false>(I, t, lds_dyn, st, ncand, !spec, deadline);
       else
-        status = run_tree<kPath == kPathTree>(I, t, &st, spec, deadline);
+        status = kPath == kPathTree ? run_tree<true>(I, t, &st, spec, deadline)
+                                    : call_tree(I, t, (ASI_LDS RelaxState*)&st, spec, deadline);
       spec = false;
     }
   }
