@@ -240,6 +240,14 @@ void launch_field(const InstDev* insts, RunDev* runs, const int32_t* blk_inst,
 inline bool relax_may_speculate(int32_t D, int32_t waves) {
   return waves == kMaxRelaxWaves && D <= kSpecMaxD;
 }
+// Sizes and degrees of the speculative batches by tiles: 8,192 tiles of 64 keys
+// take 106,496 bytes of LDS, a member's neighbours one wavefront; below, the
+// window's batches are faster (both sides are measured at relax_many).
+constexpr int64_t kManyMaxN = (int64_t)1 << 19;
+constexpr int kManyMinD = 17, kManyMaxD = 64;
+inline __host__ __device__ bool many_fits(int64_t n, int32_t D) {
+  return n <= kManyMaxN && D >= kManyMinD && D <= kManyMaxD;
+}
 // Whether its one-at-a-time relax holds every key in LDS: where they fit (a
 // thread owns at most 60 magnets, a row's byte offset has 32 bits) and the
 // parameters lie in the range of the approximated keys.
@@ -277,8 +285,8 @@ void launch_set_run(RunDev* run, int32_t* ccount, int64_t t, int64_t t_end, int3
 constexpr int32_t kPoolOverflow = -3;
 // Dynamic LDS of the relax and fused kernels for an instance of n magnets: of
 // the tree and speculative paths, and of those with keys in LDS.
-size_t relax_lds_bytes(int64_t n, int32_t l1_shift);
-size_t relax_keys_lds_bytes(int64_t n, int32_t waves, bool spec);
+size_t relax_lds_bytes(int64_t n, int32_t D, int32_t waves, int32_t l1_shift);
+size_t relax_keys_lds_bytes(int64_t n, int32_t D, int32_t waves);
 int32_t relax_l1_shift(int64_t n);
 // Raise the dynamic-LDS limit of the relax kernels (call once per process).
 hipError_t configure_kernels();

@@ -1017,6 +1017,15 @@ constexpr int kSwitchBatches = 16;
 // fewer than nine flips each on average.
 constexpr int kSwitchBatchesLds = 4;
 constexpr double kSwitchFlips = 2.5, kSwitchFlipsLds = 9.0;
+// A batch by tiles (relax_many) costs about a flip on the max tree, so those
+// steps stay (36,180-magnet pinwheel at 24 neighbours 2.2 -> 1.4 us a flip).
+// With keys in LDS a flip costs a third of a batch, but a step that starts
+// with small batches often grows them again: going over below 1.5 flips a batch
+// over four batches takes 0.80 us a flip on a 30,000-magnet kagome at 32
+// neighbours (below 3: 1.12, never: 0.77) and 50 ms on the 29,040-magnet
+// reversal at 60 neighbours, which is one avalanche (never: 129 ms).
+constexpr int kManySwitchBatches = 4;
+constexpr double kManySwitchLds = 1.5;
 
 // Relax order of two magnets: larger key first, then lower index.
 __device__ inline bool better(double ka, uint32_t pa, double kb, uint32_t pb) {
@@ -2443,6 +2452,37 @@ struct RelaxCount {
   uint64_t hash;
 };
 
+// ------------------------------------------------------------ speculative relax, tiles
+// Speculative batches without a sorted window, for up to kManyMaxN magnets and
+// kManyMaxD neighbours: of each tile of 64 consecutive magnets LDS holds the
+// largest key, its place and a bound of the second, and of each of 256 rows of
+// tiles the two largest keys.  The rows' bests that beat every row's second are
+// the first magnets of the relax order.
+constexpr int kManyMembers = 32;
+constexpr int kManyHash = 2048;  // conflict table slots (at most 1,056 in use)
+constexpr int kManyList = 1088;  // tiles that a batch changes (at most 1,056)
+constexpr int kManyRows = 256;
+
+struct ManyShared {
+  double best[kManyRows], sec[kManyRows];  // per row: largest key, (at most) the second,
+  uint32_t idx[kManyRows];                 //   the largest's magnet
+  uint32_t stale[kManyRows / 4];           // a byte per row: a tile of it changed
+  double ck[kManyRows];                    // candidates: key, magnet
+  uint32_t ci[kManyRows];
+  double mk[kManyMembers];                 // members, best first: key,
+  uint32_t mi[2][kManyMembers];            //   magnet (two sets, by turns),
+  unsigned long long vm[kManyMembers];     //   its neighbours' largest new key (bits)
+  alignas(16) int pe, nt, nc, npow, pause;  // end of the prefix; changed tiles; candidates; keys to evaluate
+};
+
+__host__ __device__ inline int many_tiles(int64_t n) {  // rounded up to whole rows
+  return (int)((((n + 63) >> 6) + 4 * kManyRows - 1) & ~(int64_t)(4 * kManyRows - 1));
+}
+__host__ __device__ inline size_t many_lds_bytes(int64_t n) {
+  const size_t tiles = (size_t)many_tiles(n);
+  return sizeof(ManyShared) + tiles * 13 + (size_t)1024 * 25 + kManyHash * 4 + tiles / 8 + kManyList * 2;
+}
+
 union RelaxParts {
   RelaxShared tree;
   SpecShared spec;
@@ -2762,6 +2802,444 @@ __device__ __forceinline__ int relax_lds(const InstDev* __restrict__ I, int64_t 
   return status;
 }
 
+// The two largest values of a group of lanes from each lane's two.
+template <int CTRL>
+__device__ __forceinline__ void top2_step(double& m, double& s) {
+  const double om = dpp_f64<CTRL>(m), os = dpp_f64<CTRL>(s);
+  s = fmax(fmax(s, os), fmin(m, om));
+  m = fmax(m, om);
+}
+// Relax at step t in speculative batches by tiles (needs 1024 threads).  A
+// batch takes the rows' bests that beat every row's second, in their order, as
+// many as the workgroup has a lane for each neighbour (if there is none, the
+// largest key alone).  A wavefront, or half of one, loads its member's row and
+// its neighbours' state and looks whether they meet another member's in the
+// conflict table; the FP64 powers of the new keys go to dense lanes; the prefix
+// that the one-at-a-time relax would flip in this order (see above) is
+// committed.  16 lanes then scan each changed tile again, and each row that owns
+// one.
+// What bounds it: a chain of eight phases a barrier apart, 13,000-15,000 cycles
+// a batch: the tiles (one trip to memory, 2,000), their rows (2,000), the
+// candidates and their ranks (2,600), the members' rows and neighbours (two
+// trips, 4,400; the rows of coming members are loaded ahead into the cache),
+// the powers (2,500: one dense pass instead of one per wavefront, which took
+// 4,400) and the commit.  Magnets whose key stays 0 leave their tile alone: 15
+// tiles a batch instead of 39.  Against the window's batches it has no sorts,
+// no merges and no refills (21,000 cycles a batch of about the same members):
+// 120,000-magnet kagome at 32 neighbours 1.04 -> 0.71 us a flip, 40,000
+// 1.45 -> 0.78, 500,000 0.94 -> 0.75, 60,000-magnet square at 60 neighbours
+// 3.08 -> 1.93 (its members crowd: 1.9 a batch, the cost of a max-tree flip
+// either way).  Below 17 neighbours the window's batches win, which take up to
+// 64 members where this takes 32 (30,000-magnet kagome at 4 neighbours 0.20
+// against 0.46), and above 2^19 magnets, where LDS would hold tiles of 128
+// (1M-magnet kagome 0.46 against 0.48).
+// Returns as relax_spec.
+__device__ __forceinline__ int relax_many(const InstDev* __restrict__ I, int64_t t, RelaxState& st,
+                                          int64_t ncand, uint64_t deadline) {
+  ManyShared& sh = *(ManyShared*)lds_dyn;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r16 = tid >> 4, l16 = tid & 15;  // the lane's place among those that scan a tile or a row
+  const int NT = 1024;
+  const int32_t n = (int32_t)I->n;
+  const int32_t D = I->D;
+  const int ntp = many_tiles(n), span = ntp / kManyRows;
+  const uint32_t span_inv = 0xffffffffu / (uint32_t)span + 1u;  // row of a tile: exact below 2^16
+  const int wsh = D > 32 ? 6 : 5;             // lanes per member
+  const int m = tid >> wsh, slot = lane & ((1 << wsh) - 1);  // the lane's member, its place there
+  const int Bmax = NT >> wsh;
+  double* const T1 = (double*)(lds_dyn + sizeof(ManyShared));       // per tile: largest key
+  double* const pw = T1 + ntp;                // keys to evaluate: field components,
+  double* const ph = pw + 2 * NT;             //   h_k,
+  uint32_t* const T2 = (uint32_t*)(ph + NT);  // per tile: a bound of the second (upper word),
+  uint32_t* const hown = T2 + ntp;
+  uint32_t* const bits = hown + kManyHash;     // tile listed
+  uint16_t* const list = (uint16_t*)(bits + ntp / 32);
+  uint8_t* const pm = (uint8_t*)(list + kManyList);  //   member (keys to evaluate)
+  uint8_t* const tp = pm + NT;                       //   the largest's place (tiles)
+
+  const int32_t mode = I->field_mode;
+  const bool carry = mode == kFieldCarry;
+  const double pb = I->b, pc = I->c, ep = I->e_par, eq = I->e_perp, pbc = pb / pc;
+  const int64_t left0 = I->max_flips - uniform(st.c.flips);  // flips this call may make
+  const int64_t logpos = uniform(st.c.logpos);
+  uint64_t hash = st.c.hash;  // the last wavefront's
+  int64_t done = 0;
+  ASI_GLOBAL double* const key = I->key;
+  ASI_GLOBAL double2* const hh = I->h;
+  ASI_GLOBAL double2* const hd = I->hd;
+  const double sw = I->spec_switch > 0.0 ? I->spec_switch : I->lds_keys != 0 ? kManySwitchLds : 0.0;
+  int64_t done1 = 0;
+  int nbatch = 0;
+
+  for (int q = tid; q < ntp; q += NT) {
+    T1[q] = 0.0;
+    T2[q] = 0u;
+  }
+  for (int q = tid; q < ntp / 32; q += NT) bits[q] = 0u;
+  for (int q = tid; q < kManyHash; q += NT) hown[q] = 0u;
+  if (tid < kManyRows) {
+    sh.best[tid] = 0.0;
+    sh.sec[tid] = 0.0;
+    sh.idx[tid] = 0u;
+    ((uint8_t*)sh.stale)[tid] = 0;
+  }
+  if (tid == 0) {
+    sh.nt = 0;
+    sh.pause = 0;
+  }
+  __syncthreads();
+  for (int64_t q = tid; q < ncand; q += NT) {
+    const uint32_t tl = (I->cpay[0][q] & 0x7fffffffu) >> 6;
+    atomicOr(&bits[tl >> 5], 1u << (tl & 31u));
+  }
+  __syncthreads();
+  // a tile's two largest keys, by 16 lanes, each with four consecutive keys
+  auto rescan_tile = [&](uint32_t tl) {
+    const uint32_t i0 = tl * 64u + (uint32_t)(l16 * 4);
+    const uint32_t last = (uint32_t)(n - 1) & ~1u;  // (n odd: its second lies in the allocation's padding)
+    const ASI_GLOBAL double2* const k2 = (const ASI_GLOBAL double2*)key;
+    const double2 v0 = load_at(k2, min(i0, last) * 8u), v1 = load_at(k2, min(i0 + 2, last) * 8u);
+    double m = 0.0, s2 = 0.0;
+    uint32_t at = 0;
+    auto take = [&](double x, uint32_t place) {
+      x = i0 + place < (uint32_t)n ? x : 0.0;
+      s2 = fmax(s2, fmin(m, x));
+      at = x > m ? place : at;
+      m = fmax(m, x);
+    };
+    take(v0.x, 0);
+    take(v0.y, 1);
+    take(v1.x, 2);
+    take(v1.y, 3);
+    const double mine = m;
+    top2_step<0xB1>(m, s2);
+    top2_step<0x4E>(m, s2);
+    top2_step<0x141>(m, s2);
+    top2_step<0x140>(m, s2);
+    // the first lane that has it: the lowest magnet among equal keys
+    const uint32_t has = (uint32_t)(__ballot(mine == m) >> (lane & 48)) & 0xffffu;
+    if (l16 == __ffs(has) - 1) {
+      T1[tl] = m;
+      T2[tl] = s2 > 0.0 ? (uint32_t)(__double_as_longlong(s2) >> 32) + 1u : 0u;
+      tp[tl] = (uint8_t)(l16 * 4 + at);
+      const uint32_t r = __umulhi(tl, span_inv);
+      ((uint8_t*)sh.stale)[(r & 63u) * 4u + (r >> 6)] = 1;
+    }
+  };
+  for (int w0 = r16; w0 < ntp / 32; w0 += 64) {
+    uint32_t b = bits[w0];
+    while (b) {
+      const int q = __ffs(b) - 1;
+      b &= b - 1u;
+      rescan_tile((uint32_t)(w0 * 32 + q));
+    }
+    if (l16 == 0) bits[w0] = 0u;
+  }
+  // list a tile whose keys changed, once
+  auto touch = [&](uint32_t i) {
+    const uint32_t tl = i >> 6, b = 1u << (tl & 31u);
+    if (!(atomicOr(&bits[tl >> 5], b) & b)) list[atomicAdd(&sh.nt, 1)] = (uint16_t)tl;
+  };
+  // conflict table: magnet + 1 and the first member there.  Of the members
+  // that meet at a magnet all but the first end the prefix.
+  auto meet = [&](uint32_t i) {
+    const uint32_t want = (i + 1u) << 5 | (uint32_t)m;
+    uint32_t q = (i * 2654435761u) >> (32 - 11);
+    while (true) {
+      uint32_t old = atomicCAS(&hown[q], 0u, want);
+      if (old == 0u) break;
+      if ((old ^ want) >> 5 == 0u) {
+        old = atomicMin(&hown[q], want);
+        const int first = (int)(old & 31u);
+        if (first != m) atomicMin(&sh.pe, first > m ? first : m);
+        break;
+      }
+      q = (q + 1) & (kManyHash - 1);
+    }
+    return (int)q;
+  };
+
+  int status = 0;
+  int set = 0;
+  int fold_n = 0;  // members of the last batch, to be folded into the hash
+  auto fold = [&]() {
+    if (wave != kMaxRelaxWaves - 1) return;
+    const uint32_t jr = sh.mi[set ^ 1][lane & (kManyMembers - 1)];
+    // times 2^40 + 435, in two words of the scalar unit
+    uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)hash);
+    uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(hash >> 32));
+    for (int r = 0; r < fold_n; ++r) {
+      lo ^= (uint32_t)__builtin_amdgcn_readlane((int)jr, r);
+      hi ^= (uint32_t)t;
+      hi = hi * 435u + __umulhi(lo, 435u) + (lo << 8);
+      lo *= 435u;
+    }
+    hash = (uint64_t)hi << 32 | lo;
+  };
+  uint32_t ahead[3] = {0u, 0u, 0u}, seen = 0u;  // loaded ahead into the cache; used by nobody
+  while (true) {
+    // ---- changed tiles
+    __syncthreads();
+    const int nt = sh.nt;
+    for (int r = r16; r < nt; r += 64) {
+      const uint32_t tl = list[r];
+      rescan_tile(tl);
+      if (l16 == 0) atomicAnd(&bits[tl >> 5], ~(1u << (tl & 31u)));
+    }
+    __syncthreads();
+    // ---- their rows
+    uint32_t stale = sh.stale[r16];  // of the 16 lanes' rows, every 64th
+    if (__ballot(stale != 0u)) {
+      if (l16 == 0 && stale != 0u) sh.stale[r16] = 0u;
+      uint32_t at = 0xffffffffu;
+      while (stale) {
+        const int r = r16 + ((__ffs(stale) - 1) >> 3) * 64;
+        stale &= stale - 1u;
+        double x = 0.0, s2 = 0.0;
+        at = 0xffffffffu;
+        for (int u = l16; u < span; u += 16) {
+          const int tl = r * span + u;
+          const double a = T1[tl], b = __longlong_as_double((long long)((uint64_t)T2[tl] << 32));
+          const uint32_t place = (uint32_t)tl << 6 | tp[tl];
+          s2 = fmax(fmax(s2, b), fmin(x, a));
+          at = a > x ? place : at;
+          x = fmax(x, a);
+        }
+        const double mine = x;
+        top2_step<0xB1>(x, s2);
+        top2_step<0x4E>(x, s2);
+        top2_step<0x141>(x, s2);
+        top2_step<0x140>(x, s2);
+        at = ~row_max_u32(mine == x ? ~at : 0u);
+        if (l16 == 0) {
+          sh.best[r] = x;
+          sh.sec[r] = s2;
+          sh.idx[r] = at;
+        }
+      }
+      if (at < (uint32_t)n) {  // a future member: its row on its way to the cache
+        seen ^= ahead[0] ^ ahead[1];
+        const int64_t e = (int64_t)at * D;
+        ahead[0] = __float_as_uint(*(const ASI_GLOBAL float*)&I->rAB[e + min(l16 * 8, D - 1)]);
+        ahead[1] = (uint32_t)I->rcol[e + min(l16 * 32, D - 1)];
+      }
+    }
+    if (tid < kManyMembers) sh.vm[tid] = 0ull;
+    if (tid == 0) {
+      sh.pe = kManyMembers;
+      sh.nt = 0;
+      sh.nc = 0;
+      sh.npow = 0;
+      if (deadline) sh.pause = (done > 0 && past(deadline)) ? 1 : 0;
+    }
+    __syncthreads();
+    // ---- the candidates: the rows' bests above every second
+    {
+      const double2 c = ((const double2*)sh.sec)[2 * lane], d = ((const double2*)sh.sec)[2 * lane + 1];
+      const int r = wave * (kManyRows / kMaxRelaxWaves) + l16;
+      const double rk = sh.best[r];
+      const uint32_t ri = sh.idx[r];
+      const double T = wave_max_f64(fmax(fmax(c.x, c.y), fmax(d.x, d.y)));
+      const bool is = lane < kManyRows / kMaxRelaxWaves && rk > T;
+      const unsigned long long bal = __ballot(is);
+      if (bal) {
+        int base = 0;
+        if (lane == 0) base = atomicAdd(&sh.nc, __popcll(bal));
+        base = __builtin_amdgcn_readfirstlane(base);
+        if (is) {
+          const int q = base + __popcll(bal & ((1ull << lane) - 1ull));
+          sh.ck[q] = rk;
+          sh.ci[q] = ri;
+        }
+      }
+    }
+    __syncthreads();
+    // ---- the members: the candidates by rank
+    uint32_t* const mi = sh.mi[set];
+    const int nc = sh.nc;
+    int B = min(nc, Bmax);
+    if (nc == 0) {  // the largest key, the lowest magnet among equal ones
+      const double2 c = ((const double2*)sh.best)[2 * lane], d = ((const double2*)sh.best)[2 * lane + 1];
+      const double x = wave_max_f64(fmax(fmax(c.x, c.y), fmax(d.x, d.y)));
+      if (!(x > 0.0)) break;
+      const uint4 e = ((const uint4*)sh.idx)[lane];
+      const uint32_t i = ~wave_max_u32(max(max(c.x == x ? ~e.x : 0u, c.y == x ? ~e.y : 0u),
+                                           max(d.x == x ? ~e.z : 0u, d.y == x ? ~e.w : 0u)));
+      if (tid == 0) {
+        sh.mk[0] = x;
+        mi[0] = i;
+      }
+      B = 1;
+    } else {
+      for (int q = wave; q < nc; q += kMaxRelaxWaves) {
+        const double c = sh.ck[q];
+        const uint32_t ci = sh.ci[q];
+        int rank = 0;
+        for (int u = lane; u - lane < nc; u += 64) {
+          const double k = u < nc ? sh.ck[u] : 0.0;
+          const uint32_t ki = u < nc ? sh.ci[u] : 0u;
+          rank += __popcll(__ballot(k > c || (k == c && ki < ci)));
+        }
+        if (rank < Bmax && lane == 0) {
+          sh.mk[rank] = c;
+          mi[rank] = ci;
+        }
+      }
+    }
+    __syncthreads();
+    if (deadline && sh.pause) {  // flippable magnets remain
+      status = 1;
+      break;
+    }
+    if (done >= left0) {
+      status = -5;
+      break;
+    }
+    // ---- the members' rows, their neighbours' state, conflicts and fields
+    const bool on = m < B;
+    uint32_t j = 0, i = 0;
+    int32_t i0 = -1;
+    int hs = -1, hj = -1, sj = 0, si = 0;
+    double2 ab = make_double2(0.0, 0.0), nh = ab, nd = ab;
+    double hki = 0.0, old = 0.0;
+    if (on) {
+      j = mi[m];
+      if (slot < D) {
+        const int64_t sl = (int64_t)j * D + slot;
+        i0 = I->rcol[sl];
+        ab = I->rAB[sl];
+      }
+      sj = load_at(I->s, j);
+      // its tile, scanned next, on its way to the cache
+      seen ^= ahead[2];
+      ahead[2] = __float_as_uint(*(const ASI_GLOBAL float*)&key[min((j & ~63u) + (uint32_t)(slot & 3) * 16u, (uint32_t)n - 1u)]);
+      if (slot == 0) hj = meet(j);
+    }
+    if (fold_n) fold();
+    i = (uint32_t)max(i0, 0);
+    if (i0 >= 0) {
+      nh = load_at(hh, i * 16u);
+      hki = load_at(I->hk, i * 8u);
+      si = load_at(I->s, i);
+      old = load_at(key, i * 8u);
+      if (carry) nd = load_at(hd, i * 16u);
+      hs = meet(i);
+    }
+    const bool down = sj < 0;
+    int pos = -1;
+    if (wave << (6 - wsh) < B) {
+      const double two = down ? 2.0 : -2.0;  // 2 s_new
+      const double da = two * ab.x, db = two * ab.y;
+      nh = make_double2(nh.x + da, nh.y + db);
+      nd = make_double2(nd.x + da, nd.y + db);
+      bool need = i0 >= 0 && (si > 0 ? nh.x < 0.0 : nh.x > 0.0);
+      if (need) {
+        // the bound of key_needs_powers, its quotients from a reciprocal within
+        // 2^-22, far inside the bound's margin; not a number is evaluated
+        const double g = __builtin_amdgcn_rcp(pb * hki);
+        const float e = pow_bound(fabs(nh.x) * g, ep) + pow_bound(fabs(nh.y) * g * pbc, eq);
+        need = !(e < 1.0f);
+      }
+      const unsigned long long bal = __ballot(need);
+      if (bal) {
+        int base = 0;
+        if (lane == 0) base = atomicAdd(&sh.npow, __popcll(bal));
+        base = __builtin_amdgcn_readfirstlane(base);
+        if (need) {
+          pos = base + __popcll(bal & ((1ull << lane) - 1ull));
+          pw[2 * pos] = fabs(nh.x);
+          pw[2 * pos + 1] = fabs(nh.y);
+          ph[pos] = hki;
+          pm[pos] = (uint8_t)m;
+        }
+      }
+    }
+    __syncthreads();
+    // ---- the powers, one per lane: the even lane's term and the odd lane's
+    const int npow = sh.npow;
+    int pe = min(sh.pe, B);
+    if (npow) {
+      for (int e = tid; e < 2 * npow; e += NT) {
+        const double r = pow_far(pw[e] / (((e & 1) ? pc : pb) * ph[e >> 1]), (e & 1) ? eq : ep);
+        const double L = r + dpp_f64<0xB1>(r);  // quad_perm [1,0,3,2]
+        if (!(e & 1)) {
+          pw[e] = (L > 1.0) ? L : 0.0;
+          if (L > 1.0) atomicMax(&sh.vm[pm[e >> 1]], (unsigned long long)__double_as_longlong(L));
+        }
+      }
+      __syncthreads();
+      // a new key that beats a later member ends the prefix there
+      const double km = sh.mk[lane & (kManyMembers - 1)];
+      const double vm = __longlong_as_double((long long)sh.vm[lane & (kManyMembers - 1)]);
+      unsigned long long b = __ballot(lane < pe && vm >= readlane_f64(km, pe - 1));
+      while (b) {
+        const int q = __ffsll(b) - 1;
+        b &= b - 1ull;
+        const unsigned long long over = __ballot(lane > q && lane < pe && km <= readlane_f64(vm, q));
+        if (over) pe = __ffsll(over) - 1;
+        if (q >= pe) break;
+      }
+    }
+    // ---- commit the prefix
+    int p = pe;
+    if (p > left0 - done) p = (int)(left0 - done);
+    if (hs >= 0) hown[hs] = 0u;  // the conflict table is left empty
+    if (hj >= 0) hown[hj] = 0u;
+    if (m < p) {
+      if (i0 >= 0) {
+        const double nkey = pos >= 0 ? pw[2 * pos] : 0.0;
+        if (nkey != old) {
+          store_at(key, i * 8u, nkey);
+          touch(i);
+        }
+        store_at(hh, i * 16u, nh);
+        if (carry)
+          store_at(hd, i * 16u, nd);
+        else if (mode == kFieldDirty)
+          store_at(I->dirty, i, (uint8_t)1);
+      }
+      if (slot == 0) {
+        store_at(key, j * 8u, 0.0);
+        touch(j);
+        store_at(I->s, j, down ? (int8_t)1 : (int8_t)-1);
+        const int64_t q = logpos + done + m;
+        if (q < I->log_cap) {
+          I->log_t[q] = (int32_t)t;
+          I->log_j[q] = (int32_t)j;
+        }
+      }
+    }
+    fold_n = p;
+    set ^= 1;
+    done += p;
+    if (++nbatch == kManySwitchBatches) {
+      if ((double)(done - done1) < sw * kManySwitchBatches) {
+        status = 2;
+        break;
+      }
+      nbatch = 0;
+      done1 = done;
+    }
+  }
+  fold();  // the last batch's flips
+  __syncthreads();
+  if (tid < kManyRows) sh.ci[tid] = seen ^ ahead[0] ^ ahead[1] ^ ahead[2];  // (their use)
+  if (tid == NT - 1) {
+    st.c.flips += done;
+    st.c.logpos = logpos + done;
+    st.c.hash = hash;
+  }
+  __syncthreads();
+  return status;
+}
+
+__device__ __attribute__((noinline)) int call_many(const InstDev* I, int64_t t, ASI_LDS RelaxState* st,
+                                                   int64_t ncand, uint64_t deadline) {
+  return relax_many(uniform(I), uniform(t), *(RelaxState*)st, uniform(ncand),
+                    (uint64_t)uniform((int64_t)deadline));
+}
+
 __device__ __forceinline__ int run_spec(const InstDev* I, int64_t t, RelaxState* st, int64_t ncand,
                                        uint64_t deadline) {
   int64_t flips = uniform(st->c.flips), logpos = uniform(st->c.logpos);
@@ -2807,6 +3285,18 @@ __device__ __attribute__((noinline)) void call_field(const InstDev* I0, int64_t 
   __syncthreads();
 }
 
+// Whether a step with ncand flippable magnets starts with batches.  Up to
+// kManyFromN magnets (a thread's tile of codes is one 16-byte read there) one
+// flip at a time is faster than batches by tiles, unless a threshold is set:
+// 972- and 3,072-magnet kagome at 32 neighbours 1.8 and 1.3 us a flip against
+// 2.5 and 1.6; 6,075 and 10,092 magnets 1.4 and 1.5 against 1.2 and 1.1.
+constexpr int64_t kManyFromN = 4096;
+template <bool kLds>
+__device__ __forceinline__ bool start_spec(const InstDev* __restrict__ I, int64_t ncand) {
+  if (I->D > kSpecMaxD || ncand < I->spec_min) return false;
+  return !(kLds && I->n <= kManyFromN && many_fits(I->n, I->D) && I->spec_min == kSpecMinDefault);
+}
+
 // Relax one instance at step t (Sec. II.H) and advance its run cursor.
 // Steps that start with enough flippable magnets (spec_min, and a degree that
 // leaves room for batches) take the speculative path; the others, and a
@@ -2828,10 +3318,10 @@ __device__ __forceinline__ int relax_step(const InstDev* __restrict__ I, RunDev*
     status = kPoolOverflow;  // cannot happen while every pass starts from an empty pool
   } else {
     if constexpr (kPath == kPathSpec || kPath == kPathLdsSpec) {
-      spec = blockDim.x == 1024 &&
-             (R->paused ? R->spec != 0 : (I->D <= kSpecMaxD && ncand >= I->spec_min));
+      spec = blockDim.x == 1024 && (R->paused ? R->spec != 0 : start_spec<kLds>(I, ncand));
       if (spec)
-        status = kLds ? call_spec(I, t, (ASI_LDS RelaxState*)&st, ncand, deadline)
+        status = many_fits(I->n, I->D) ? call_many(I, t, (ASI_LDS RelaxState*)&st, ncand, deadline)
+                 : kLds ? call_spec(I, t, (ASI_LDS RelaxState*)&st, ncand, deadline)
                       : run_spec(I, t, &st, ncand, deadline);
     }
     if (status == 2) {
@@ -3526,20 +4016,27 @@ int32_t relax_l1_shift(int64_t n) {
   return s;
 }
 
-size_t relax_lds_bytes(int64_t n, int32_t l1_shift) {
-  // one relax path runs per step, so the two share the space
-  const size_t a = relax_tree_lds_bytes(n, l1_shift), b = spec_lds_bytes();
-  return a > b ? a : b;
+namespace {
+size_t batch_lds_bytes(int64_t n, int32_t D) {
+  return many_fits(n, D) ? many_lds_bytes(n) : spec_lds_bytes();
+}
+}  // namespace
+
+// the relax paths of a step share the space
+size_t relax_lds_bytes(int64_t n, int32_t D, int32_t waves, int32_t l1_shift) {
+  const size_t a = relax_tree_lds_bytes(n, l1_shift);
+  return relax_may_speculate(D, waves) ? std::max(a, batch_lds_bytes(n, D)) : a;
 }
 
-size_t relax_keys_lds_bytes(int64_t n, int32_t waves, bool spec) {
+size_t relax_keys_lds_bytes(int64_t n, int32_t D, int32_t waves) {
   const size_t a = flip_lds_bytes(n, 64 * waves);
-  return spec ? std::max(a, spec_lds_bytes()) : a;
+  return relax_may_speculate(D, waves) ? std::max(a, batch_lds_bytes(n, D)) : a;
 }
 
 hipError_t configure_kernels() {
   // the relax kernels take more than 64 KB of dynamic LDS
-  const int tree = (int)relax_lds_bytes((int64_t)kMaxL1Tiles << 6, 6);
+  const int tree = (int)std::max({relax_tree_lds_bytes((int64_t)kMaxL1Tiles << 6, 6), spec_lds_bytes(),
+                                  many_lds_bytes(kManyMaxN)});
   const int keys = (int)flip_lds_bytes(kLdsMaxN, 64 * kMaxRelaxWaves);
   const std::pair<const void*, int> k[] = {
       {reinterpret_cast<const void*>(&k_relax<kPathTree>), tree},

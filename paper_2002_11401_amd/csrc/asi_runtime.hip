@@ -285,7 +285,8 @@ void set_relax_path(asi_sim* s) {
   const bool spec = relax_may_speculate(s->D, s->relax_waves);
   s->hI.lds_keys = keys ? 1 : 0;
   s->path = relax_path(keys, spec);
-  s->lds = keys ? relax_keys_lds_bytes(s->n, s->relax_waves, spec) : relax_lds_bytes(s->n, s->l1s);
+  s->lds = keys ? relax_keys_lds_bytes(s->n, s->D, s->relax_waves)
+                : relax_lds_bytes(s->n, s->D, s->relax_waves, s->l1s);
 }
 
 asi_status create_impl(const asi_params* p, const asi_device* dev, asi_sim* s) {
@@ -1559,8 +1560,8 @@ asi_status table_build(Table& T, std::vector<InstDev>& insts, const std::vector<
     Table::Group& g = I.lds_keys ? T.keys : T.other;
     g.any = true;
     g.spec |= spec;
-    g.lds = std::max(g.lds, I.lds_keys ? relax_keys_lds_bytes(I.n, T.waves, spec)
-                                       : relax_lds_bytes(I.n, I.l1_shift));
+    g.lds = std::max(g.lds, I.lds_keys ? relax_keys_lds_bytes(I.n, I.D, T.waves)
+                                       : relax_lds_bytes(I.n, I.D, T.waves, I.l1_shift));
   }
   if (T.keys.any && T.other.any && !T.open_side())
     return fail(ASI_EDEVICE, "stream creation failed (batch)");
