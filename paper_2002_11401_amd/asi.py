@@ -354,7 +354,7 @@ class Sim:
         idx = np.ascontiguousarray(idx, dtype=np.int32)
         if len(ptr) < 2 or ptr[-1] > len(idx):
             raise ValueError("ptr must have G+1 entries ending at most at len(idx)")
-        out = np.zeros((len(ptr) - 1, 2))
+        out = np.empty((len(ptr) - 1, 2))
         idx_buf = idx if len(idx) else np.zeros(1, np.int32)   # held across the call
         _check(library().asi_group_magnetization(self.handle, len(ptr) - 1, _ptr(ptr),
                                                  _ptr(idx_buf), _ptr(out)))
@@ -363,7 +363,7 @@ class Sim:
     def switching_order(self) -> np.ndarray:
         """[n]: flip-log position of each magnet's first switch (the log's
         length for magnets that never switched), computed on the device."""
-        out = np.zeros(self.n, dtype=np.int64)
+        out = np.empty(self.n, dtype=np.int64)
         _check(library().asi_switching_order(self.handle, _ptr(out)))
         return out
 
@@ -392,9 +392,9 @@ class Sim:
         _check(library().asi_compute_fields(self.handle, int(t)))
 
     def state(self):
-        s = np.zeros(self.n, dtype=np.int8)
-        hp = np.zeros(self.n)
-        hq = np.zeros(self.n)
+        s = np.empty(self.n, dtype=np.int8)  # filled whole, or not returned
+        hp = np.empty(self.n)
+        hq = np.empty(self.n)
         step = C.c_int64(0)
         _check(library().asi_get_state(self.handle, _ptr(s), _ptr(hp), _ptr(hq), C.byref(step)))
         return s, hp, hq, step.value
@@ -410,8 +410,8 @@ class Sim:
         h = C.c_uint64(0)
         _check(library().asi_get_flip_log(self.handle, 0, None, None, C.byref(cnt), C.byref(h)))
         m = cnt.value if cap is None else min(cap, cnt.value)
-        st = np.zeros(max(m, 1), dtype=np.int32)
-        ix = np.zeros(max(m, 1), dtype=np.int32)
+        st = np.empty(max(m, 1), dtype=np.int32)
+        ix = np.empty(max(m, 1), dtype=np.int32)
         _check(library().asi_get_flip_log(self.handle, m, _ptr(st), _ptr(ix), C.byref(cnt),
                                           C.byref(h)))
         got = min(m, cnt.value, self.info()["flip_log_capacity"])
