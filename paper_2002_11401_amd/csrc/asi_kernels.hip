@@ -15,7 +15,11 @@
 //   k_relax                 one workgroup per instance: argmax over the
 //                           flippable keys (ties: lowest index), flip, update
 //                           the neighbours' fields incrementally, repeat
-//                           until none can flip (Sec. II.H)
+//                           until none can flip (Sec. II.H); several
+//                           paths with the same flips: one at a time on a
+//                           max tree or on approximated keys in LDS, and
+//                           exact-order batches from a sorted window or from
+//                           tile maxima
 //   k_fused                 one workgroup per instance runs whole steps
 //                           (field phase + relax) through its own protocol
 #include <algorithm>

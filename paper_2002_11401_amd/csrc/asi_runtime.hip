@@ -383,8 +383,10 @@ bool read_items(asi_sim* s, const void* src, int64_t items, size_t width, F take
   HostBuffers::Lease buf;
   host_buffers().take((size_t)items * width, buf);
   if (!buf.p) return false;
+  int device = -1;  // the pieces' events are made on the current device
+  const bool cut = hipGetDevice(&device) == hipSuccess && device == s->device;
   const int pieces = (int)std::max<int64_t>(
-      1, std::min<int64_t>(kMostPieces, (int64_t)((size_t)items * width / kPieceBytes)));
+      1, std::min<int64_t>(cut ? kMostPieces : 1, (int64_t)((size_t)items * width / kPieceBytes)));
   auto start = [&](int k) { return items * k / pieces; };
   const unsigned char* dev = static_cast<const unsigned char*>(src);
   hipEvent_t done[kMostPieces] = {};
