@@ -241,9 +241,10 @@ inline bool relax_may_speculate(int32_t D, int32_t waves) {
   return waves == kMaxRelaxWaves && D <= kSpecMaxD;
 }
 // Sizes and degrees of the speculative batches by tiles: 8,192 tiles of 64 keys
-// take 106,496 bytes of LDS, a member's neighbours one wavefront; below, the
-// window's batches are faster (both sides are measured at relax_many).
-constexpr int64_t kManyMaxN = (int64_t)1 << 19;
+// (128 above 2^19 magnets) take 106,496 bytes of LDS, a member's neighbours one
+// wavefront; elsewhere the window's batches are faster (both sides are measured
+// at relax_many).
+constexpr int64_t kManyMaxN64 = (int64_t)1 << 19, kManyMaxN = (int64_t)1 << 20;
 constexpr int kManyMinD = 17, kManyMaxD = 64;
 inline __host__ __device__ bool many_fits(int64_t n, int32_t D) {
   return n <= kManyMaxN && D >= kManyMinD && D <= kManyMaxD;

@@ -25,6 +25,7 @@
 #include <algorithm>
 #include <climits>
 #include <mutex>
+#include <type_traits>
 #include <utility>
 
 #define ASI_KERNELS_UNIT 1
@@ -2465,26 +2466,43 @@ struct RelaxCount {
 constexpr int kManyMembers = 32;
 constexpr int kManyHash = 2048;  // conflict table slots (at most 1,056 in use)
 constexpr int kManyList = 1088;  // tiles that a batch changes (at most 1,056)
-constexpr int kManyRows = 256;
+// Up to 2^19 magnets tiles of 64 in 256 rows, above tiles of 128 in 512 rows:
+// half the tiles, and twice the rows for the more candidates of such sizes (a
+// 1M-magnet kagome's field window 17.6 ms a pass against 18.0 with 256 rows; a
+// 200,000-magnet square 1.91 us a flip with 256 rows against 2.06).
+constexpr int kManyRows = 256, kManyRowsBig = 512;
 
+template <int kRows>
 struct ManyShared {
-  double best[kManyRows], sec[kManyRows];  // per row: largest key, (at most) the second,
-  uint32_t idx[kManyRows];                 //   the largest's magnet
-  uint32_t stale[kManyRows / 4];           // a byte per row: a tile of it changed
-  double ck[kManyRows];                    // candidates: key, magnet
-  uint32_t ci[kManyRows];
+  double best[kRows], sec[kRows];  // per row: largest key, (at most) the second,
+  uint32_t idx[kRows];                 //   the largest's magnet
+  using Stale = std::conditional_t<kRows == 256, uint32_t, unsigned long long>;
+  Stale stale[64];                         // a byte per row: a tile of it changed
+  double ck[kRows];                    // candidates: key, magnet
+  uint32_t ci[kRows];
   double mk[kManyMembers];                 // members, best first: key,
   uint32_t mi[2][kManyMembers];            //   magnet (two sets, by turns),
   unsigned long long vm[kManyMembers];     //   its neighbours' largest new key (bits)
   alignas(16) int pe, nt, nc, npow, pause;  // end of the prefix; changed tiles; candidates; keys to evaluate
 };
 
-__host__ __device__ inline int many_tiles(int64_t n) {  // rounded up to whole rows
-  return (int)((((n + 63) >> 6) + 4 * kManyRows - 1) & ~(int64_t)(4 * kManyRows - 1));
+template <int kRows>
+__host__ __device__ constexpr int many_tile_shift() {
+  return kRows == kManyRows ? 6 : 7;
 }
-__host__ __device__ inline size_t many_lds_bytes(int64_t n) {
-  const size_t tiles = (size_t)many_tiles(n);
-  return sizeof(ManyShared) + tiles * 13 + (size_t)1024 * 25 + kManyHash * 4 + tiles / 8 + kManyList * 2;
+template <int kRows>
+__host__ __device__ inline int many_tiles(int64_t n) {  // rounded up to whole rows
+  const int sh = many_tile_shift<kRows>();
+  return (int)((((n + (1 << sh) - 1) >> sh) + 4 * kRows - 1) & ~(int64_t)(4 * kRows - 1));
+}
+template <int kRows>
+__host__ __device__ inline size_t many_lds(int64_t n) {
+  const size_t tiles = (size_t)many_tiles<kRows>(n);
+  return sizeof(ManyShared<kRows>) + tiles * 13 + (size_t)1024 * 25 + kManyHash * 4 + tiles / 8 +
+         kManyList * 2;
+}
+inline size_t many_lds_bytes(int64_t n) {
+  return n <= kManyMaxN64 ? many_lds<kManyRows>(n) : many_lds<kManyRowsBig>(n);
 }
 
 union RelaxParts {
@@ -2835,24 +2853,27 @@ __device__ __forceinline__ void top2_step(double& m, double& s) {
 // 3.08 -> 1.93 (its members crowd: 1.9 a batch, the cost of a max-tree flip
 // either way).  Below 17 neighbours the window's batches win, which take up to
 // 64 members where this takes 32 (30,000-magnet kagome at 4 neighbours 0.20
-// against 0.46), and above 2^19 magnets, where LDS would hold tiles of 128
-// (1M-magnet kagome 0.46 against 0.48).
+// against 0.46).  Above 2^19 magnets: square at 60 neighbours, 641,000, 2.7 ->
+// 2.2, 1M-magnet kagome reversal 0.94 -> 0.74.
 // Returns as relax_spec.
+template <int kRows>
 __device__ __forceinline__ int relax_many(const InstDev* __restrict__ I, int64_t t, RelaxState& st,
                                           int64_t ncand, uint64_t deadline) {
-  ManyShared& sh = *(ManyShared*)lds_dyn;
+  using Shared = ManyShared<kRows>;
+  Shared& sh = *(Shared*)lds_dyn;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = tid >> 4, l16 = tid & 15;  // the lane's place among those that scan a tile or a row
   const int NT = 1024;
   const int32_t n = (int32_t)I->n;
   const int32_t D = I->D;
-  const int ntp = many_tiles(n), span = ntp / kManyRows;
+  constexpr int tsh = many_tile_shift<kRows>();  // tiles of 64 or 128
+  const int ntp = many_tiles<kRows>(n), span = ntp / kRows;
   const uint32_t span_inv = 0xffffffffu / (uint32_t)span + 1u;  // row of a tile: exact below 2^16
   const int wsh = D > 32 ? 6 : 5;             // lanes per member
   const int m = tid >> wsh, slot = lane & ((1 << wsh) - 1);  // the lane's member, its place there
   const int Bmax = NT >> wsh;
-  double* const T1 = (double*)(lds_dyn + sizeof(ManyShared));       // per tile: largest key
+  double* const T1 = (double*)(lds_dyn + sizeof(Shared));       // per tile: largest key
   double* const pw = T1 + ntp;                // keys to evaluate: field components,
   double* const ph = pw + 2 * NT;             //   h_k,
   uint32_t* const T2 = (uint32_t*)(ph + NT);  // per tile: a bound of the second (upper word),
@@ -2882,7 +2903,7 @@ __device__ __forceinline__ int relax_many(const InstDev* __restrict__ I, int64_t
   }
   for (int q = tid; q < ntp / 32; q += NT) bits[q] = 0u;
   for (int q = tid; q < kManyHash; q += NT) hown[q] = 0u;
-  if (tid < kManyRows) {
+  if (tid < kRows) {
     sh.best[tid] = 0.0;
     sh.sec[tid] = 0.0;
     sh.idx[tid] = 0u;
@@ -2894,16 +2915,21 @@ __device__ __forceinline__ int relax_many(const InstDev* __restrict__ I, int64_t
   }
   __syncthreads();
   for (int64_t q = tid; q < ncand; q += NT) {
-    const uint32_t tl = (I->cpay[0][q] & 0x7fffffffu) >> 6;
+    const uint32_t tl = (I->cpay[0][q] & 0x7fffffffu) >> tsh;
     atomicOr(&bits[tl >> 5], 1u << (tl & 31u));
   }
   __syncthreads();
-  // a tile's two largest keys, by 16 lanes, each with four consecutive keys
+  // a tile's two largest keys, by 16 lanes, each with four or eight consecutive keys
   auto rescan_tile = [&](uint32_t tl) {
-    const uint32_t i0 = tl * 64u + (uint32_t)(l16 * 4);
+    const uint32_t i0 = (tl << tsh) + ((uint32_t)l16 << (tsh - 4));
     const uint32_t last = (uint32_t)(n - 1) & ~1u;  // (n odd: its second lies in the allocation's padding)
     const ASI_GLOBAL double2* const k2 = (const ASI_GLOBAL double2*)key;
-    const double2 v0 = load_at(k2, min(i0, last) * 8u), v1 = load_at(k2, min(i0 + 2, last) * 8u);
+    auto pair = [&](uint32_t u) { return load_at(k2, min(i0 + u, last) * 8u); };
+    double2 v0 = pair(0), v1 = pair(2), v2, v3;
+    if (tsh > 6) {
+      v2 = pair(4);
+      v3 = pair(6);
+    }
     double m = 0.0, s2 = 0.0;
     uint32_t at = 0;
     auto take = [&](double x, uint32_t place) {
@@ -2916,6 +2942,12 @@ __device__ __forceinline__ int relax_many(const InstDev* __restrict__ I, int64_t
     take(v0.y, 1);
     take(v1.x, 2);
     take(v1.y, 3);
+    if (tsh > 6) {
+      take(v2.x, 4);
+      take(v2.y, 5);
+      take(v3.x, 6);
+      take(v3.y, 7);
+    }
     const double mine = m;
     top2_step<0xB1>(m, s2);
     top2_step<0x4E>(m, s2);
@@ -2926,9 +2958,9 @@ __device__ __forceinline__ int relax_many(const InstDev* __restrict__ I, int64_t
     if (l16 == __ffs(has) - 1) {
       T1[tl] = m;
       T2[tl] = s2 > 0.0 ? (uint32_t)(__double_as_longlong(s2) >> 32) + 1u : 0u;
-      tp[tl] = (uint8_t)(l16 * 4 + at);
+      tp[tl] = (uint8_t)(((uint32_t)l16 << (tsh - 4)) + at);
       const uint32_t r = __umulhi(tl, span_inv);
-      ((uint8_t*)sh.stale)[(r & 63u) * 4u + (r >> 6)] = 1;
+      ((uint8_t*)sh.stale)[(r & 63u) * (kRows / 64) + (r >> 6)] = 1;
     }
   };
   for (int w0 = r16; w0 < ntp / 32; w0 += 64) {
@@ -2942,8 +2974,18 @@ __device__ __forceinline__ int relax_many(const InstDev* __restrict__ I, int64_t
   }
   // list a tile whose keys changed, once
   auto touch = [&](uint32_t i) {
-    const uint32_t tl = i >> 6, b = 1u << (tl & 31u);
+    const uint32_t tl = i >> tsh, b = 1u << (tl & 31u);
     if (!(atomicOr(&bits[tl >> 5], b) & b)) list[atomicAdd(&sh.nt, 1)] = (uint16_t)tl;
+  };
+  // the largest of a lane's share of the rows' values
+  auto max_of_lane = [&](const double* v) {
+    double x = 0.0;
+#pragma unroll
+    for (int u = 0; u < kRows / 128; ++u) {
+      const double2 e = ((const double2*)v)[u * 64 + lane];
+      x = fmax(x, fmax(e.x, e.y));
+    }
+    return x;
   };
   // conflict table: magnet + 1 and the first member there.  Of the members
   // that meet at a magnet all but the first end the prefix.
@@ -2993,19 +3035,20 @@ __device__ __forceinline__ int relax_many(const InstDev* __restrict__ I, int64_t
     }
     __syncthreads();
     // ---- their rows
-    uint32_t stale = sh.stale[r16];  // of the 16 lanes' rows, every 64th
-    if (__ballot(stale != 0u)) {
-      if (l16 == 0 && stale != 0u) sh.stale[r16] = 0u;
+    // of the 16 lanes' rows, every 64th
+    typename Shared::Stale stale = sh.stale[r16];
+    if (__ballot(stale != 0)) {
+      if (l16 == 0 && stale != 0) sh.stale[r16] = 0;
       uint32_t at = 0xffffffffu;
       while (stale) {
-        const int r = r16 + ((__ffs(stale) - 1) >> 3) * 64;
-        stale &= stale - 1u;
+        const int r = r16 + ((__ffsll((unsigned long long)stale) - 1) >> 3) * 64;
+        stale &= stale - 1;
         double x = 0.0, s2 = 0.0;
         at = 0xffffffffu;
         for (int u = l16; u < span; u += 16) {
           const int tl = r * span + u;
           const double a = T1[tl], b = __longlong_as_double((long long)((uint64_t)T2[tl] << 32));
-          const uint32_t place = (uint32_t)tl << 6 | tp[tl];
+          const uint32_t place = (uint32_t)tl << tsh | tp[tl];
           s2 = fmax(fmax(s2, b), fmin(x, a));
           at = a > x ? place : at;
           x = fmax(x, a);
@@ -3040,12 +3083,12 @@ __device__ __forceinline__ int relax_many(const InstDev* __restrict__ I, int64_t
     __syncthreads();
     // ---- the candidates: the rows' bests above every second
     {
-      const double2 c = ((const double2*)sh.sec)[2 * lane], d = ((const double2*)sh.sec)[2 * lane + 1];
-      const int r = wave * (kManyRows / kMaxRelaxWaves) + l16;
+      constexpr int kOwn = kRows / kMaxRelaxWaves;  // rows of a wavefront
+      const int r = wave * kOwn + (lane & (kOwn - 1));
       const double rk = sh.best[r];
       const uint32_t ri = sh.idx[r];
-      const double T = wave_max_f64(fmax(fmax(c.x, c.y), fmax(d.x, d.y)));
-      const bool is = lane < kManyRows / kMaxRelaxWaves && rk > T;
+      const double T = wave_max_f64(max_of_lane(sh.sec));
+      const bool is = lane < kOwn && rk > T;
       const unsigned long long bal = __ballot(is);
       if (bal) {
         int base = 0;
@@ -3064,12 +3107,13 @@ __device__ __forceinline__ int relax_many(const InstDev* __restrict__ I, int64_t
     const int nc = sh.nc;
     int B = min(nc, Bmax);
     if (nc == 0) {  // the largest key, the lowest magnet among equal ones
-      const double2 c = ((const double2*)sh.best)[2 * lane], d = ((const double2*)sh.best)[2 * lane + 1];
-      const double x = wave_max_f64(fmax(fmax(c.x, c.y), fmax(d.x, d.y)));
+      const double x = wave_max_f64(max_of_lane(sh.best));
       if (!(x > 0.0)) break;
-      const uint4 e = ((const uint4*)sh.idx)[lane];
-      const uint32_t i = ~wave_max_u32(max(max(c.x == x ? ~e.x : 0u, c.y == x ? ~e.y : 0u),
-                                           max(d.x == x ? ~e.z : 0u, d.y == x ? ~e.w : 0u)));
+      uint32_t i = 0u;
+#pragma unroll
+      for (int u = 0; u < kRows / 64; ++u)
+        i = max(i, sh.best[u * 64 + lane] == x ? ~sh.idx[u * 64 + lane] : 0u);
+      i = ~wave_max_u32(i);
       if (tid == 0) {
         sh.mk[0] = x;
         mi[0] = i;
@@ -3117,7 +3161,7 @@ __device__ __forceinline__ int relax_many(const InstDev* __restrict__ I, int64_t
       sj = load_at(I->s, j);
       // its tile, scanned next, on its way to the cache
       seen ^= ahead[2];
-      ahead[2] = __float_as_uint(*(const ASI_GLOBAL float*)&key[min((j & ~63u) + (uint32_t)(slot & 3) * 16u, (uint32_t)n - 1u)]);
+      ahead[2] = __float_as_uint(*(const ASI_GLOBAL float*)&key[min((j >> tsh << tsh) + (uint32_t)(slot & 7) * 16u, (uint32_t)n - 1u)]);
       if (slot == 0) hj = meet(j);
     }
     if (fold_n) fold();
@@ -3228,7 +3272,7 @@ __device__ __forceinline__ int relax_many(const InstDev* __restrict__ I, int64_t
   }
   fold();  // the last batch's flips
   __syncthreads();
-  if (tid < kManyRows) sh.ci[tid] = seen ^ ahead[0] ^ ahead[1] ^ ahead[2];  // (their use)
+  if (tid < kRows) sh.ci[tid] = seen ^ ahead[0] ^ ahead[1] ^ ahead[2];  // (their use)
   if (tid == NT - 1) {
     st.c.flips += done;
     st.c.logpos = logpos + done;
@@ -3238,9 +3282,10 @@ __device__ __forceinline__ int relax_many(const InstDev* __restrict__ I, int64_t
   return status;
 }
 
+template <int kRows>
 __device__ __attribute__((noinline)) int call_many(const InstDev* I, int64_t t, ASI_LDS RelaxState* st,
                                                    int64_t ncand, uint64_t deadline) {
-  return relax_many(uniform(I), uniform(t), *(RelaxState*)st, uniform(ncand),
+  return relax_many<kRows>(uniform(I), uniform(t), *(RelaxState*)st, uniform(ncand),
                     (uint64_t)uniform((int64_t)deadline));
 }
 
@@ -3324,9 +3369,12 @@ __device__ __forceinline__ int relax_step(const InstDev* __restrict__ I, RunDev*
     if constexpr (kPath == kPathSpec || kPath == kPathLdsSpec) {
       spec = blockDim.x == 1024 && (R->paused ? R->spec != 0 : start_spec<kLds>(I, ncand));
       if (spec)
-        status = many_fits(I->n, I->D) ? call_many(I, t, (ASI_LDS RelaxState*)&st, ncand, deadline)
-                 : kLds ? call_spec(I, t, (ASI_LDS RelaxState*)&st, ncand, deadline)
-                      : run_spec(I, t, &st, ncand, deadline);
+        status = !many_fits(I->n, I->D)
+                     ? (kLds ? call_spec(I, t, (ASI_LDS RelaxState*)&st, ncand, deadline)
+                             : run_spec(I, t, &st, ncand, deadline))
+                 : kLds || I->n <= kManyMaxN64
+                     ? call_many<kManyRows>(I, t, (ASI_LDS RelaxState*)&st, ncand, deadline)
+                     : call_many<kManyRowsBig>(I, t, (ASI_LDS RelaxState*)&st, ncand, deadline);
     }
     if (status == 2) {
       if constexpr (kLds)

@@ -1,4 +1,4 @@
-"""Speculative batches by tiles (up to 2^19 magnets, 17 to 64 neighbours):
+"""Speculative batches by tiles (up to 2^20 magnets, 17 to 64 neighbours):
 flips, spins and fields bit for bit those of the one-at-a-time relax on the max
 tree, at the sizes and parameters where they can go wrong."""
 import dataclasses
@@ -12,7 +12,7 @@ from test_relax_lds import LDS_MAX_N, assert_oracle, assert_same, result
 from test_relax_lds import line as narrow_line
 
 pytestmark = pytest.mark.gpu
-MANY_MAX_N = 1 << 19
+SMALL_TILES_MAX_N, MANY_MAX_N = 1 << 19, 1 << 20
 TREE = dict(spec_min=10**12)  # no speculation: the max tree where keys are not in LDS
 
 
@@ -28,9 +28,9 @@ def spec_and_tree(w, **kw):
 
 
 # part of a tile, a tile and one more, the rows once and once more, the largest
-# size and the first beyond it
+# size of small tiles and the next, the largest size and the first beyond it
 @pytest.mark.parametrize("n", [21, 64, 65, 8191, LDS_MAX_N + 1, 65536, 65537,
-                               MANY_MAX_N, MANY_MAX_N + 1])
+                               SMALL_TILES_MAX_N, SMALL_TILES_MAX_N + 1, MANY_MAX_N, MANY_MAX_N + 1])
 def test_sizes(n):
     w = line(n, steps=3 if n > 100000 else 10)
     r, tree = spec_and_tree(w)
