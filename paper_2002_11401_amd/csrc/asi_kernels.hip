@@ -2518,7 +2518,7 @@ struct RelaxState {
 // Relax at step t, one flip at a time.  Each thread owns a tile of
 // consecutive magnets and keeps its largest code in a register.  Per flip:
 //   - the wavefronts' best codes give the winner, whose row is loaded.  If no
-//     other code lies within kCodeNear of it, and it is surely above 1, it is
+//     other code reaches its floor (code_floor), and it is surely above 1, it is
 //     the magnet the exact keys would pick; else the exact FP64 keys of the
 //     codes that near decide (keys of 0 are struck out, equal keys go to the
 //     lower index); an exact key is kept in the key array until the magnet's
