@@ -2957,7 +2957,8 @@ __device__ __forceinline__ int relax_many(const InstDev* __restrict__ I, int64_t
     const uint32_t has = (uint32_t)(__ballot(mine == m) >> (lane & 48)) & 0xffffu;
     if (l16 == __ffs(has) - 1) {
       T1[tl] = m;
-      T2[tl] = s2 > 0.0 ? (uint32_t)(__double_as_longlong(s2) >> 32) + 1u : 0u;
+      // (at most infinity's: one more would be not a number, which fmax passes over)
+      T2[tl] = s2 > 0.0 ? min((uint32_t)(__double_as_longlong(s2) >> 32) + 1u, 0x7ff00000u) : 0u;
       tp[tl] = (uint8_t)(((uint32_t)l16 << (tsh - 4)) + at);
       const uint32_t r = __umulhi(tl, span_inv);
       ((uint8_t*)sh.stale)[(r & 63u) * (kRows / 64) + (r >> 6)] = 1;
