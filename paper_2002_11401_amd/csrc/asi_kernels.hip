@@ -77,13 +77,16 @@ __device__ inline void thermal_normals(uint64_t seed, uint32_t i, uint32_t t, do
   z1 = rad * sn;
 }
 
-// Upper bound of x^e (x >= 0, e > 0) from the single-precision hardware
-// log2 and exp2, inflated by 0.1 %, far past their error (a few units in
-// the 24th bit of the exponent and of the result); x below 2^-100 is raised
-// to 2^-100, which only raises x^e.
+// Upper bound of x^e (x >= 0, e > 0, x within 2^-22) from the
+// single-precision hardware log2 and exp2: the exponent e log2 x is raised by
+// e 2^-20, past the error of log2 x (x's own, its 24 bits and a few units of
+// the hardware's: below 6e-7, whatever e), and by log2(1.001), far past that
+// of the product and of exp2; x below 2^-100 is raised to 2^-100, which only
+// raises x^e.
 __device__ inline float pow_bound(double x, double e) {
-  const float xf = (float)fmax(x, 0x1p-100);
-  return __builtin_amdgcn_exp2f((float)e * __builtin_amdgcn_logf(xf)) * 1.001f;
+  const float xf = (float)fmax(x, 0x1p-100), ef = (float)e;
+  return __builtin_amdgcn_exp2f(
+      __builtin_fmaf(ef, __builtin_amdgcn_logf(xf), ef * 0x1p-20f + 0.00144197f));
 }
 
 // Switching key: the left-hand side of Eq. 5 when magnet i may flip, i.e.
@@ -3185,7 +3188,7 @@ __device__ __forceinline__ int relax_many(const InstDev* __restrict__ I, int64_t
       bool need = i0 >= 0 && (si > 0 ? nh.x < 0.0 : nh.x > 0.0);
       if (need) {
         // the bound of key_needs_powers, its quotients from a reciprocal within
-        // 2^-22, far inside the bound's margin; not a number is evaluated
+        // 2^-22, which the bound allows for; not a number is evaluated
         const double g = __builtin_amdgcn_rcp(pb * hki);
         const float e = pow_bound(fabs(nh.x) * g, ep) + pow_bound(fabs(nh.y) * g * pbc, eq);
         need = !(e < 1.0f);

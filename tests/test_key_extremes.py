@@ -1,4 +1,5 @@
-"""Left-hand sides of Eq. 5 above the FP64 range, which tie at infinity, on
+"""Left-hand sides of Eq. 5 above the FP64 range, which tie at infinity, and
+exponents at which a component's last bits decide whether a magnet can flip, on
 every path of the relax: flips, spins and fields bit for bit those of the max
 tree, and the oracle's."""
 import dataclasses
@@ -39,3 +40,23 @@ def test_infinite_keys(n, distance, case):
     assert_same(result(w), tree)
     if n < 50000:
         assert_oracle(w, r)
+
+
+@pytest.mark.parametrize("distance", [2.0, 10.0, 70.0])
+@pytest.mark.parametrize("case", ["one term", "two terms"])
+def test_large_exponents(distance, case):
+    """2 / gamma = 10^6: every left-hand side lies between 1 and 1.05, from
+    components that differ from 1 by less than 10^-6."""
+    n, e = 5000, 1e6
+    w = dataclasses.replace(line(n, steps=3), neighbor_distance=distance, alpha=0.0, beta=2.0 / e, gamma=2.0 / e)
+    lhs = 1.0 + np.random.default_rng(8).permutation(np.linspace(1e-3, 0.05, n))
+    if case == "one term":
+        w.H, w.c = np.array([[0.2, 0.0], [0.1, 0.0], [-0.2, 0.0]]), np.inf
+        w.hk = 0.2 / np.exp(np.log(lhs) / e)
+    else:
+        w.H = np.array([[0.2, 0.0], [0.1, 0.0], [-0.2, 0.2]])
+        w.hk = 0.2 / np.exp(np.log(lhs / 2.0) / e)
+    r, tree = spec_and_tree(w)
+    assert r["flips"] == n
+    assert_same(r, tree)
+    assert_oracle(w, r)
