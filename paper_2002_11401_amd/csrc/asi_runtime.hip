@@ -95,6 +95,11 @@ struct DevMem {
 // pinned for the copy, in 460 us, or 1,750 us where its pages are new).  A call
 // takes a buffer and gives it back; at most kKeep bytes wait for the next call,
 // and none once the last handle is gone.
+// Pinning a new buffer costs about 0.25 ms and 0.2 ms a MB.  Below kAtOnce a
+// single transfer does not earn that back (3.2 MB of fields, first read: 0.56 ms
+// from pageable memory, 1.0-1.5 with a new buffer, 0.22 with one at hand), so
+// the process's first transfer of a size class finds none and goes without;
+// from there on it does (8 MB: 2.2 ms, 1.3-1.7, 0.4).
 class HostBuffers {
  public:
   struct Lease {
@@ -123,6 +128,10 @@ class HostBuffers {
           free_.pop_back();
           return;
         }
+      if (cap < kAtOnce && !(asked_ & cap)) {
+        asked_ |= cap;
+        return;
+      }
     }
     if (cap > kMost) return;
     void* p = nullptr;
@@ -150,6 +159,7 @@ class HostBuffers {
 
  private:
   static constexpr size_t kLeast = (size_t)64 << 10, kMost = (size_t)64 << 20, kKeep = (size_t)96 << 20;
+  static constexpr size_t kAtOnce = (size_t)8 << 20;
   void give(unsigned char* p, size_t cap) {
     {
       std::lock_guard<std::mutex> lock(m_);
@@ -166,7 +176,7 @@ class HostBuffers {
   }
   std::mutex m_;
   std::vector<std::pair<unsigned char*, size_t>> free_;
-  size_t kept_ = 0;
+  size_t kept_ = 0, asked_ = 0;  // asked_: a bit per capacity below kAtOnce
   int64_t handles_ = 0;
 };
 HostBuffers& host_buffers() {
@@ -575,31 +585,34 @@ asi_status create_impl(const asi_params* p, const asi_device* dev, asi_sim* s) {
     return fail(ASI_ENOMEM, "device allocation failed (inputs)");
   std::vector<int8_t> s0(n, 1);
   if (p->spin0) std::memcpy(s0.data(), p->spin0, n);
-  Uploads up(s->stream);
-  HIPCHK(up.put(dx, x.data(), 8 * n), s);
-  HIPCHK(up.put(dy, y.data(), 8 * n), s);
-  HIPCHK(up.put(dmx, mx.data(), 8 * n), s);
-  HIPCHK(up.put(dmy, my.data(), 8 * n), s);
+  // (one transfer of each array in a handle's life: not through pinned buffers,
+  // with which the first creation of a size took up to twice as long, 200,000
+  // magnets 5.3 -> 9.9 ms, and later ones 2 % longer)
+  HIPCHK(hipMemcpyAsync(dx, x.data(), 8 * n, hipMemcpyHostToDevice, s->stream), s);
+  HIPCHK(hipMemcpyAsync(dy, y.data(), 8 * n, hipMemcpyHostToDevice, s->stream), s);
+  HIPCHK(hipMemcpyAsync(dmx, mx.data(), 8 * n, hipMemcpyHostToDevice, s->stream), s);
+  HIPCHK(hipMemcpyAsync(dmy, my.data(), 8 * n, hipMemcpyHostToDevice, s->stream), s);
   if (p->hk) {
-    HIPCHK(up.put(dhk, p->hk, 8 * n), s);
+    HIPCHK(hipMemcpyAsync(dhk, p->hk, 8 * n, hipMemcpyHostToDevice, s->stream), s);
   } else {
     launch_draw_hk(dhk, n, p->hk_mean, p->k_disorder, p->disorder_seed, s->stream);
     HIPCHK(hipGetLastError(), s);
   }
-  HIPCHK(up.put(ds, s0.data(), n), s);
-  HIPCHK(up.put(dcx, cx.data(), 4 * n), s);
-  HIPCHK(up.put(dcy, cy.data(), 4 * n), s);
-  HIPCHK(up.put(dcs, cstart.data(), 4 * (gx * gy + 1)), s);
-  HIPCHK(up.put(dcm, cmem.data(), 4 * n), s);
+  HIPCHK(hipMemcpyAsync(ds, s0.data(), n, hipMemcpyHostToDevice, s->stream), s);
+  HIPCHK(hipMemcpyAsync(dcx, cx.data(), 4 * n, hipMemcpyHostToDevice, s->stream), s);
+  HIPCHK(hipMemcpyAsync(dcy, cy.data(), 4 * n, hipMemcpyHostToDevice, s->stream), s);
+  HIPCHK(hipMemcpyAsync(dcs, cstart.data(), 4 * (gx * gy + 1), hipMemcpyHostToDevice, s->stream),
+         s);
+  HIPCHK(hipMemcpyAsync(dcm, cmem.data(), 4 * n, hipMemcpyHostToDevice, s->stream), s);
   HIPCHK(hipMemsetAsync(ddup, 0, 4, s->stream), s);
 
   // device: neighbour counts -> padded row length
   launch_neighbour_count(dx, dy, dcx, dcy, dcs, dcm, n, gx, gy, cut2, dlen, ddup, s->stream);
   std::vector<int32_t> len(n);
   int32_t dup = 0;
+  HIPCHK(hipMemcpyAsync(len.data(), dlen, 4 * n, hipMemcpyDeviceToHost, s->stream), s);
   HIPCHK(hipMemcpyAsync(&dup, ddup, 4, hipMemcpyDeviceToHost, s->stream), s);
-  const asi_status rd = read_bytes(s, len.data(), dlen, 4 * (size_t)n);
-  if (rd != ASI_OK) return rd;
+  HIPCHK(hipStreamSynchronize(s->stream), s);
   if (dup) return fail(ASI_EINVAL, "coincident magnets (zero separation)");
   int64_t E = 0;
   int32_t D = 0;
@@ -735,9 +748,11 @@ asi_status create_impl(const asi_params* p, const asi_device* dev, asi_sim* s) {
   HIPCHK(hipMemsetAsync(I.dirty, 1, n, s->stream), s);
   std::vector<int32_t> bi(s->nblocks, 0), br(s->nblocks);
   for (int64_t b = 0; b < s->nblocks; ++b) br[b] = (int32_t)(b * kFieldBlock);
-  HIPCHK(up.put(s->blk_inst, bi.data(), 4 * s->nblocks), s);
-  HIPCHK(up.put(s->blk_row0, br.data(), 4 * s->nblocks), s);
-  HIPCHK(up.put(s->dI, &s->hI, sizeof(InstDev)), s);
+  HIPCHK(hipMemcpyAsync(s->blk_inst, bi.data(), 4 * s->nblocks, hipMemcpyHostToDevice, s->stream),
+         s);
+  HIPCHK(hipMemcpyAsync(s->blk_row0, br.data(), 4 * s->nblocks, hipMemcpyHostToDevice, s->stream),
+         s);
+  HIPCHK(hipMemcpyAsync(s->dI, &s->hI, sizeof(InstDev), hipMemcpyHostToDevice, s->stream), s);
   launch_set_run(s->dR, I.ccount, -1, -1, 0, 1, -1, s->stream);
   return sync_and_check(s);
 }
