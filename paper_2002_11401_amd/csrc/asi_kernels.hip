@@ -2064,14 +2064,27 @@ __device__ __forceinline__ int relax_tree(const InstDev* __restrict__ I, int64_t
   // waited for at once (45,300-magnet pinwheel reversal at 632 neighbours 357 ms,
   // 337 so).
   int64_t pf_j = -1;
-  int32_t pf_c[2] = {-1, -1};
-  f64x2 pf_ab[2] = {{0.0, 0.0}, {0.0, 0.0}};
+  constexpr int kAhead = kFlatOk ? 2 : 1;  // slots a thread (as many as the registers allow)
+  int32_t pf_c[kAhead];
+  f64x2 pf_ab[kAhead];
+#pragma unroll
+  for (int h = 0; h < kAhead; ++h) {
+    pf_c[h] = -1;
+    pf_ab[h] = f64x2{0.0, 0.0};
+  }
 
   // Up to kFlatTiles tiles the root reads the first level directly (at most
   // eight ascending tiles per lane) and the second level is not kept; only
   // in the tree-only kernel, whose registers allow it.
   const bool flat = kFlatOk && nt1 <= kFlatTiles;
   const int per1 = (nt1 + 63) >> 6;
+  // tid, where registers are short as a value of this flip: addresses formed
+  // from it are formed again, which is cheaper than their way to memory and back
+  auto own = [&]() {
+    int v = tid;
+    if (!kFlatOk) asm volatile("" : "+v"(v));
+    return v;
+  };
 
   while (true) {
     if (wave == 0) {
@@ -2169,21 +2182,22 @@ __device__ __forceinline__ int relax_tree(const InstDev* __restrict__ I, int64_t
     // whose loads the wavefront has waited for, so they are complete; using
     // the registers here makes that known, and no wait below is widened to
     // them.
-    asm volatile("" ::"v"(pf_c[0]), "v"(pf_c[1]), "v"(pf_ab[0]), "v"(pf_ab[1]));
+#pragma unroll
+    for (int h = 0; h < kAhead; ++h) asm volatile("" ::"v"(pf_c[h]), "v"(pf_ab[h]));
     int u_i[2], u_e[2], u_s[2];
     double u_k[2];
     double tb_k = 0.0;  // this thread's best updated key, for the prediction
     uint32_t tb_i = 0;
 #pragma unroll
     for (int h = 0; h < 2; ++h) u_i[h] = -1;
-    for (int k = tid, h = 0; k < D; k += NT, ++h) {
+    for (int k = own(), h = 0; k < D; k += NT, ++h) {
       const int64_t sl = j * D + k;
-      const bool pre = hit && h < 2;
+      const bool pre = hit && h < kAhead;
       // the slot's column and couplings together (a padding slot holds -1
       // and zeros), then every load of the neighbour's state before any
       // store, so that each costs one round trip
-      const int32_t i = pre ? pf_c[h & 1] : colp[sl];
-      const f64x2 cab = pre ? pf_ab[h & 1] : ABp[sl];
+      const int32_t i = pre ? pf_c[h & (kAhead - 1)] : colp[sl];
+      const f64x2 cab = pre ? pf_ab[h & (kAhead - 1)] : ABp[sl];
       const double ca = cab.x, cb = cab.y;
       if (i >= 0) {
         const double2 hi = hp2[i];
@@ -2278,7 +2292,7 @@ __device__ __forceinline__ int relax_tree(const InstDev* __restrict__ I, int64_t
       pf_j = pk ? (int64_t)(pk & 0xffffffffull) : -1;
       if (pf_j >= 0) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
+        for (int h = 0; h < kAhead; ++h) {
           const int k = tid + h * NT;
           if (k < D) {
             const int64_t sl = pf_j * D + k;
@@ -2300,7 +2314,7 @@ __device__ __forceinline__ int relax_tree(const InstDev* __restrict__ I, int64_t
     if (tid == 0) sh.pfk = 0ull;  // every thread has read it
     // touched tiles: a scan of the flags (nt1 <= kMaxL1Tiles), each tile's
     // state read at once
-    for (int e = tid; e < nt1; e += NT) {
+    for (int e = own(); e < nt1; e += NT) {
       if (!L.l1flag[e]) continue;
       if (L.l1resc[e]) {
         L.l1rlist[atomicAdd(&sh.nr, 1)] = e;
@@ -2550,7 +2564,6 @@ template <bool kTile1>
 __device__ __forceinline__ int relax_lds(const InstDev* __restrict__ I, int64_t t, unsigned char* lds_raw,
                                          RelaxState& st, int64_t ncand, bool from_pool,
                                          uint64_t deadline) {
-  if (from_pool && ncand == 0) return 0;  // nothing can flip
   FlipShared& sh = st.u.flip;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int NT = blockDim.x;
@@ -3324,12 +3337,6 @@ __device__ __forceinline__ int run_tree(const InstDev* I, int64_t t, RelaxState*
   return status;
 }
 
-__device__ __attribute__((noinline)) int call_tree(const InstDev* I, int64_t t, ASI_LDS RelaxState* st,
-                                                   bool rebuild, uint64_t deadline) {
-  return run_tree<false>(uniform(I), uniform(t), (RelaxState*)st, rebuild,
-                         (uint64_t)uniform((int64_t)deadline));
-}
-
 // The field phase of a whole instance by one workgroup.
 __device__ __attribute__((noinline)) void call_field(const InstDev* I0, int64_t t, bool resume) {
   const InstDev* I = uniform(I0);
@@ -3358,6 +3365,9 @@ __device__ __forceinline__ bool start_spec(const InstDev* __restrict__ I, int64_
 // key in LDS where they fit (kPathLds, kPathLdsSpec), else on the max tree
 // (kPathTree, kPathSpec).  A paused step resumes on the path it was on.  All
 // flip exactly the magnets, in exactly the order, of the one-at-a-time relax.
+// The one-at-a-time relax is inline: called, it stored and loaded some 60
+// registers a lane at each step, 2-3 us (a step of 40,000 magnets without flips
+// took 12 us instead of 9.8; 6.8 now), and had registers of its loop spilled.
 template <int kPath>
 __device__ __forceinline__ int relax_step(const InstDev* __restrict__ I, RunDev* __restrict__ R, int64_t t,
                           RelaxState& st, uint64_t deadline) {
@@ -3370,6 +3380,8 @@ __device__ __forceinline__ int relax_step(const InstDev* __restrict__ I, RunDev*
   int status = 2;
   if ((int64_t)(uint32_t)ncand > I->ccap) {
     status = kPoolOverflow;  // cannot happen while every pass starts from an empty pool
+  } else if (ncand == 0) {
+    status = 0;  // nothing can flip (the field phase lists every magnet that can)
   } else {
     if constexpr (kPath == kPathSpec || kPath == kPathLdsSpec) {
       spec = blockDim.x == 1024 && (R->paused ? R->spec != 0 : start_spec<kLds>(I, ncand));
@@ -3387,8 +3399,7 @@ __device__ __forceinline__ int relax_step(const InstDev* __restrict__ I, RunDev*
                      ? relax_lds<true>(I, t, lds_dyn, st, ncand, !spec, deadline)
                      : relax_lds<false>(I, t, lds_dyn, st, ncand, !spec, deadline);
       else
-        status = kPath == kPathTree ? run_tree<true>(I, t, &st, spec, deadline)
-                                    : call_tree(I, t, (ASI_LDS RelaxState*)&st, spec, deadline);
+        status = run_tree<kPath == kPathTree>(I, t, &st, spec, deadline);
       spec = false;
     }
   }
@@ -3454,7 +3465,7 @@ __global__ __launch_bounds__(64 * kMaxRelaxWaves) void k_fused(const InstDev* __
   RunDev* R = runs + blockIdx.x;
   const bool paused = R->paused != 0;
   if (!R->active && !paused) return;
-  const InstDev* I = insts + blockIdx.x;
+  const InstDev* I = uniform(insts + blockIdx.x);
   if (!on_path(I, kPath)) return;  // run by another launch
   __shared__ RelaxState st;
   __shared__ int go;
