@@ -50,6 +50,7 @@ enum RelaxPath : int32_t {
   kPathSpec = 1,  // speculative batches or the max tree, by step
   kPathLds = 2,   // one flip at a time, every key in LDS
   kPathLdsSpec = 3,  // speculative batches or the latter, by step
+  kPathMixed = 4,  // of a launch with instances of kPathSpec and kPathLdsSpec
 };
 
 // How the dipolar sum of a row is obtained at the start of a field step.
@@ -258,18 +259,17 @@ inline bool relax_keys_in_lds(const InstDev& I, int32_t waves) {
          I.e_perp >= 0.25 && I.e_perp <= 4.0 && I.b > 0x1p-60 && I.b < 0x1p60 &&
          I.c > 0x1p-60 && (I.c < 0x1p60 || I.b / I.c == 0.0);
 }
-// The path of an instance, or of a table's instances of one kind.
+// The path of an instance, or of a table whose instances are of one kind.
 inline RelaxPath relax_path(bool keys_in_lds, bool may_speculate) {
   return keys_in_lds ? (may_speculate ? kPathLdsSpec : kPathLds)
                      : (may_speculate ? kPathSpec : kPathTree);
 }
-// One workgroup per instance: relax the current step of the instances on
-// `path` (kPathTree or kPathLds only where none of its kind may speculate).
+// One workgroup per instance: relax the current step on `path` (kPathTree or
+// kPathLds only where no instance may speculate, kPathMixed for any).
 void launch_relax(const InstDev* insts, RunDev* runs, int32_t count, int32_t waves,
                   size_t lds_bytes, RelaxPath path, hipStream_t st);
-// One workgroup per instance, of those with keys in LDS or of the others: up to
-// max_steps whole steps (field phase and relax) per instance.  With
-// budget_ticks > 0 a workgroup stops once that many ticks of the
+// One workgroup per instance: up to max_steps whole steps (field phase and
+// relax) per instance.  With budget_ticks > 0 a workgroup stops once that many ticks of the
 // device's constant-rate clock have passed: between steps, or inside a relax
 // (which then pauses, see RunDev).  With first_ready a field launch has just
 // computed each active instance's fields and rebuilt each paused one's relax

@@ -3337,6 +3337,13 @@ __device__ __forceinline__ int run_tree(const InstDev* I, int64_t t, RelaxState*
   return status;
 }
 
+template <bool kTile1>
+__device__ __attribute__((noinline)) int call_lds(const InstDev* I, int64_t t, ASI_LDS RelaxState* st,
+                                                  int64_t ncand, bool from_pool, uint64_t deadline) {
+  return relax_lds<kTile1>(uniform(I), uniform(t), lds_dyn, *(RelaxState*)st, uniform(ncand),
+                           from_pool, (uint64_t)uniform((int64_t)deadline));
+}
+
 // The field phase of a whole instance by one workgroup.
 __device__ __attribute__((noinline)) void call_field(const InstDev* I0, int64_t t, bool resume) {
   const InstDev* I = uniform(I0);
@@ -3352,10 +3359,9 @@ __device__ __attribute__((noinline)) void call_field(const InstDev* I0, int64_t 
 // 972- and 3,072-magnet kagome at 32 neighbours 1.8 and 1.3 us a flip against
 // 2.5 and 1.6; 6,075 and 10,092 magnets 1.4 and 1.5 against 1.2 and 1.1.
 constexpr int64_t kManyFromN = 4096;
-template <bool kLds>
-__device__ __forceinline__ bool start_spec(const InstDev* __restrict__ I, int64_t ncand) {
+__device__ __forceinline__ bool start_spec(const InstDev* __restrict__ I, int64_t ncand, bool lds) {
   if (I->D > kSpecMaxD || ncand < I->spec_min) return false;
-  return !(kLds && I->n <= kManyFromN && many_fits(I->n, I->D) && I->spec_min == kSpecMinDefault);
+  return !(lds && I->n <= kManyFromN && many_fits(I->n, I->D) && I->spec_min == kSpecMinDefault);
 }
 
 // Relax one instance at step t (Sec. II.H) and advance its run cursor.
@@ -3365,13 +3371,17 @@ __device__ __forceinline__ bool start_spec(const InstDev* __restrict__ I, int64_
 // key in LDS where they fit (kPathLds, kPathLdsSpec), else on the max tree
 // (kPathTree, kPathSpec).  A paused step resumes on the path it was on.  All
 // flip exactly the magnets, in exactly the order, of the one-at-a-time relax.
-// The one-at-a-time relax is inline: called, it stored and loaded some 60
-// registers a lane at each step, 2-3 us (a step of 40,000 magnets without flips
-// took 12 us instead of 9.8; 6.8 now), and had registers of its loop spilled.
+// kPathMixed holds the parts of kPathSpec and kPathLdsSpec, for launches with
+// instances of both kinds.
+// The one-at-a-time relax is inline (the mixed kernel's max tree): called, it
+// stored and loaded some 60 registers a lane at each step, 2-3 us (a step of
+// 40,000 magnets without flips took 12 us instead of 9.5; 6.0 now), and had
+// registers of its loop spilled.
 template <int kPath>
 __device__ __forceinline__ int relax_step(const InstDev* __restrict__ I, RunDev* __restrict__ R, int64_t t,
                           RelaxState& st, uint64_t deadline) {
-  constexpr bool kLds = kPath == kPathLds || kPath == kPathLdsSpec;
+  constexpr bool kMixed = kPath == kPathMixed, kLds = kPath == kPathLds || kPath == kPathLdsSpec;
+  const bool lds = kMixed ? I->lds_keys != 0 : kLds;
   const int64_t ncand = __hip_atomic_load(I->ccount, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const int64_t acc0 = R->step_acc;  // flips of step t before a pause
   if (threadIdx.x == 0) st.c = RelaxCount{acc0, R->flips, R->hash};
@@ -3383,23 +3393,26 @@ __device__ __forceinline__ int relax_step(const InstDev* __restrict__ I, RunDev*
   } else if (ncand == 0) {
     status = 0;  // nothing can flip (the field phase lists every magnet that can)
   } else {
-    if constexpr (kPath == kPathSpec || kPath == kPathLdsSpec) {
-      spec = blockDim.x == 1024 && (R->paused ? R->spec != 0 : start_spec<kLds>(I, ncand));
+    if constexpr (kPath != kPathTree && kPath != kPathLds) {
+      spec = blockDim.x == 1024 && (R->paused ? R->spec != 0 : start_spec(I, ncand, lds));
       if (spec)
         status = !many_fits(I->n, I->D)
-                     ? (kLds ? call_spec(I, t, (ASI_LDS RelaxState*)&st, ncand, deadline)
-                             : run_spec(I, t, &st, ncand, deadline))
-                 : kLds || I->n <= kManyMaxN64
+                     ? (kPath == kPathSpec ? run_spec(I, t, &st, ncand, deadline)
+                                           : call_spec(I, t, (ASI_LDS RelaxState*)&st, ncand, deadline))
+                 : lds || I->n <= kManyMaxN64
                      ? call_many<kManyRows>(I, t, (ASI_LDS RelaxState*)&st, ncand, deadline)
                      : call_many<kManyRowsBig>(I, t, (ASI_LDS RelaxState*)&st, ncand, deadline);
     }
     if (status == 2) {
+      const bool tile1 = flip_tile(I->n, (int)blockDim.x) == 4;
       if constexpr (kLds)
-        status = flip_tile(I->n, (int)blockDim.x) == 4
-                     ? relax_lds<true>(I, t, lds_dyn, st, ncand, !spec, deadline)
-                     : relax_lds<false>(I, t, lds_dyn, st, ncand, !spec, deadline);
-      else
+        status = tile1 ? relax_lds<true>(I, t, lds_dyn, st, ncand, !spec, deadline)
+                       : relax_lds<false>(I, t, lds_dyn, st, ncand, !spec, deadline);
+      else if (!kMixed || !lds)
         status = run_tree<kPath == kPathTree>(I, t, &st, spec, deadline);
+      else
+        status = tile1 ? call_lds<true>(I, t, (ASI_LDS RelaxState*)&st, ncand, !spec, deadline)
+                       : call_lds<false>(I, t, (ASI_LDS RelaxState*)&st, ncand, !spec, deadline);
       spec = false;
     }
   }
@@ -3429,11 +3442,6 @@ __device__ __forceinline__ int relax_step(const InstDev* __restrict__ I, RunDev*
   return status;
 }
 
-// Whether an instance is relaxed by launches on `path`.
-__device__ __forceinline__ bool on_path(const InstDev* I, int path) {
-  return (I->lds_keys != 0) == (path == kPathLds || path == kPathLdsSpec);
-}
-
 template <int kPath>
 __global__ __launch_bounds__(64 * kMaxRelaxWaves) void k_relax(const InstDev* __restrict__ insts,
                                                               RunDev* __restrict__ runs) {
@@ -3442,7 +3450,6 @@ __global__ __launch_bounds__(64 * kMaxRelaxWaves) void k_relax(const InstDev* __
   // structures rebuilt by the preceding field launch
   if (!R->active && !R->paused) return;
   const InstDev* I = insts + blockIdx.x;
-  if (!on_path(I, kPath)) return;  // relaxed by another launch
   __shared__ RelaxState st;
   relax_step<kPath>(I, R, R->t, st, 0);
 }
@@ -3466,7 +3473,6 @@ __global__ __launch_bounds__(64 * kMaxRelaxWaves) void k_fused(const InstDev* __
   const bool paused = R->paused != 0;
   if (!R->active && !paused) return;
   const InstDev* I = uniform(insts + blockIdx.x);
-  if (!on_path(I, kPath)) return;  // run by another launch
   __shared__ RelaxState st;
   __shared__ int go;
   const uint64_t t_start = wall_clock64();
@@ -4052,6 +4058,8 @@ void launch_relax(const InstDev* insts, RunDev* runs, int32_t count, int32_t wav
     hipLaunchKernelGGL(k_relax<kPathLdsSpec>, g, b, lds_bytes, st, insts, runs);
   else if (path == kPathTree)
     hipLaunchKernelGGL(k_relax<kPathTree>, g, b, lds_bytes, st, insts, runs);
+  else if (path == kPathMixed)
+    hipLaunchKernelGGL(k_relax<kPathMixed>, g, b, lds_bytes, st, insts, runs);
   else
     hipLaunchKernelGGL(k_relax<kPathSpec>, g, b, lds_bytes, st, insts, runs);
 }
@@ -4066,6 +4074,9 @@ void launch_fused(const InstDev* insts, RunDev* runs, int32_t count, int32_t wav
                        budget_ticks, first_ready);
   else if (path == kPathLdsSpec)
     hipLaunchKernelGGL(k_fused<kPathLdsSpec>, g, b, lds_bytes, st, insts, runs, max_steps,
+                       budget_ticks, first_ready);
+  else if (path == kPathMixed)
+    hipLaunchKernelGGL(k_fused<kPathMixed>, g, b, lds_bytes, st, insts, runs, max_steps,
                        budget_ticks, first_ready);
   else
     hipLaunchKernelGGL(k_fused<kPathSpec>, g, b, lds_bytes, st, insts, runs, max_steps,
@@ -4113,7 +4124,9 @@ hipError_t configure_kernels() {
       {reinterpret_cast<const void*>(&k_relax<kPathLdsSpec>), keys},
       {reinterpret_cast<const void*>(&k_fused<kPathLdsSpec>), keys},
       {reinterpret_cast<const void*>(&k_fused<kPathSpec>), tree},
-      {reinterpret_cast<const void*>(&k_fused<kPathLds>), keys}};
+      {reinterpret_cast<const void*>(&k_fused<kPathLds>), keys},
+      {reinterpret_cast<const void*>(&k_relax<kPathMixed>), std::max(tree, keys)},
+      {reinterpret_cast<const void*>(&k_fused<kPathMixed>), std::max(tree, keys)}};
   hipError_t e = hipSuccess;
   for (const auto& f : k)
     if (e == hipSuccess)

@@ -1,0 +1,36 @@
+"""Which relax runs, and how it is launched."""
+from time import perf_counter
+
+import numpy as np
+import pytest
+
+from paper_2002_11401_amd import asi
+from test_relax_lds import LDS_MAX_N, line
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("mode", ["lockstep", "graph", "fused"])
+def test_batch_of_both_kinds_costs_no_more_than_its_parts(mode):
+    """Steps without flips, launches and waits alone: instances with keys in
+    LDS and others in one batch, against the two batches one after the other."""
+    H = np.zeros((300, 2))
+    ws = [line(LDS_MAX_N + 900)] + [line(500, seed=k) for k in range(8)]
+    for w in ws:
+        w.H = H
+    sims = [asi.Sim.from_workload(w) for w in ws]
+
+    def best(part):
+        times = []
+        for _ in range(5):
+            for s in part:
+                s.set_state(np.ones(s.n, np.int8), -1)
+            t0 = perf_counter()
+            asi.batch_run(part, mode)
+            times.append(perf_counter() - t0)
+        return min(times)
+
+    both, parts = best(sims), best(sims[:1]) + best(sims[1:])
+    for s in sims:
+        s.close()
+    assert both <= parts, (both, parts)
