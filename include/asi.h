@@ -293,7 +293,9 @@ typedef struct {
                            the handle's minimum (tiles <= 2048) up to 20     */
   int64_t spec_min;     /* flippable magnets at a step's start for the
                            speculative path, >= 1 (it also needs a degree
-                           <= 128)                                           */
+                           <= 128).  Default 32; INT64_MAX (never) up to
+                           4,096 magnets at 17 to 64 neighbours, where one
+                           flip at a time is faster                         */
   double default_ms;    /* asi_tune: sample time with the shapes it found    */
   double tuned_ms;      /* asi_tune: sample time with the shapes it chose    */
   int32_t trials;       /* asi_tune: shapes timed (0: taken from the cache)  */

@@ -41,8 +41,6 @@ constexpr int kSpecMaxD = 128;
 // Most magnets whose relax keys are held in LDS (4 bytes each: 147,456 of the
 // 163,840 bytes, beside a spin bit per magnet and the workgroup's own state).
 constexpr int64_t kLdsMaxN = 36864;
-// Default of asi_tuning.spec_min.
-constexpr int64_t kSpecMinDefault = 32;
 
 // The relax of an instance, each path a kernel of its own.
 enum RelaxPath : int32_t {
@@ -258,6 +256,16 @@ inline bool relax_keys_in_lds(const InstDev& I, int32_t waves) {
          I.n * I.D < ((int64_t)1 << 28) && I.e_par >= 0.25 && I.e_par <= 4.0 &&
          I.e_perp >= 0.25 && I.e_perp <= 4.0 && I.b > 0x1p-60 && I.b < 0x1p60 &&
          I.c > 0x1p-60 && (I.c < 0x1p60 || I.b / I.c == 0.0);
+}
+// Default of asi_tuning.spec_min: 32 flippable magnets.  Up to kManyFromN magnets
+// with their keys in LDS (a thread's tile of codes is one 16-byte read there) one
+// flip at a time is faster than batches by tiles, so they never start with those:
+// 972- and 3,072-magnet kagome at 32 neighbours 1.8 and 1.3 us a flip against
+// 2.5 and 1.6; 6,075 and 10,092 magnets 1.4 and 1.5 against 1.2 and 1.1.
+constexpr int64_t kManyFromN = 4096;
+inline int64_t default_spec_min(const InstDev& I) {
+  return I.n <= kManyFromN && many_fits(I.n, I.D) && relax_keys_in_lds(I, kMaxRelaxWaves) ? INT64_MAX
+                                                                                         : 32;
 }
 // The path of an instance, or of a table whose instances are of one kind.
 inline RelaxPath relax_path(bool keys_in_lds, bool may_speculate) {

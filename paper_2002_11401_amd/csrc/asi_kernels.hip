@@ -3353,17 +3353,6 @@ __device__ __attribute__((noinline)) void call_field(const InstDev* I0, int64_t 
   __syncthreads();
 }
 
-// Whether a step with ncand flippable magnets starts with batches.  Up to
-// kManyFromN magnets (a thread's tile of codes is one 16-byte read there) one
-// flip at a time is faster than batches by tiles, unless a threshold is set:
-// 972- and 3,072-magnet kagome at 32 neighbours 1.8 and 1.3 us a flip against
-// 2.5 and 1.6; 6,075 and 10,092 magnets 1.4 and 1.5 against 1.2 and 1.1.
-constexpr int64_t kManyFromN = 4096;
-__device__ __forceinline__ bool start_spec(const InstDev* __restrict__ I, int64_t ncand, bool lds) {
-  if (I->D > kSpecMaxD || ncand < I->spec_min) return false;
-  return !(lds && I->n <= kManyFromN && many_fits(I->n, I->D) && I->spec_min == kSpecMinDefault);
-}
-
 // Relax one instance at step t (Sec. II.H) and advance its run cursor.
 // Steps that start with enough flippable magnets (spec_min, and a degree that
 // leaves room for batches) take the speculative path; the others, and a
@@ -3394,7 +3383,8 @@ __device__ __forceinline__ int relax_step(const InstDev* __restrict__ I, RunDev*
     status = 0;  // nothing can flip (the field phase lists every magnet that can)
   } else {
     if constexpr (kPath != kPathTree && kPath != kPathLds) {
-      spec = blockDim.x == 1024 && (R->paused ? R->spec != 0 : start_spec(I, ncand, lds));
+      spec = blockDim.x == 1024 && (R->paused ? R->spec != 0
+                                              : I->D <= kSpecMaxD && ncand >= I->spec_min);
       if (spec)
         status = !many_fits(I->n, I->D)
                      ? (kPath == kPathSpec ? run_spec(I, t, &st, ncand, deadline)

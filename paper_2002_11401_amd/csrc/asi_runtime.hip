@@ -723,7 +723,7 @@ asi_status create_impl(const asi_params* p, const asi_device* dev, asi_sim* s) {
   if (!I.ver || !I.ccount) return fail(ASI_ENOMEM, "device allocation failed (candidate pool)");
   HIPCHK(hipMemsetAsync(I.ver, 0, 4 * n, s->stream), s);
   HIPCHK(hipMemsetAsync(I.ccount, 0, 4, s->stream), s);
-  I.spec_min = kSpecMinDefault;
+  I.spec_min = default_spec_min(I);
   if (const char* e = std::getenv("ASI_SPEC_MIN")) I.spec_min = std::atoll(e);
   I.spec_switch = 0.0;
   if (const char* e = std::getenv("ASI_SPEC_SWITCH")) I.spec_switch = std::atof(e);
@@ -1531,7 +1531,7 @@ asi_status asi_tune(asi_handle h, int64_t sample_steps, asi_tuning* out) {
   }
   // 1. speculation threshold (only where the degree allows speculation)
   if (st == ASI_OK && h->D <= kSpecMaxD && cur.relax_waves == kMaxRelaxWaves) {
-    const int64_t mins[] = {8, 256, INT64_MAX};
+    const int64_t mins[] = {8, 32, 256, INT64_MAX};
     for (int64_t m : mins) {
       if (st != ASI_OK || m == cur.spec_min) continue;
       asi_tuning c = best;

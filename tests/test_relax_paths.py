@@ -1,11 +1,12 @@
 """Which relax runs, and how it is launched."""
+import dataclasses
 from time import perf_counter
 
 import numpy as np
 import pytest
 
 from paper_2002_11401_amd import asi
-from test_relax_lds import LDS_MAX_N, line
+from test_relax_lds import LDS_MAX_N, assert_same, line, result
 
 pytestmark = pytest.mark.gpu
 
@@ -34,3 +35,17 @@ def test_batch_of_both_kinds_costs_no_more_than_its_parts(mode):
     for s in sims:
         s.close()
     assert both <= parts, (both, parts)
+
+
+@pytest.mark.parametrize("n,never", [(4096, True), (4097, False)])
+def test_threshold_in_force(n, never):
+    """The handle reports the threshold that its steps are held to, and takes
+    every value literally, the usual default of 32 as well."""
+    w = dataclasses.replace(line(n), neighbor_distance=10.0)
+    sim = asi.Sim.from_workload(w)
+    t = sim.tuning()
+    assert t["spec_min"] == (2**63 - 1 if never else 32)
+    sim.set_tuning(t["relax_waves"], t["l1_shift"], 32)
+    assert sim.tuning()["spec_min"] == 32
+    sim.close()
+    assert_same(result(w), result(w, tuning=dict(spec_min=32)))
