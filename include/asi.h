@@ -308,9 +308,9 @@ typedef struct {
  * field steps under candidate shapes (rows per workgroup of the
  * high-degree full-field pass, speculation threshold, then tile size, then
  * workgroup size), each run from a device snapshot of the handle's state,
- * and keeps the fastest.  The result is cached per (GPU architecture,
- * floor(log2 n), floor(log2 max_degree), field_mode): a later call on a
- * handle of the same class applies the cached shapes without timing
+ * and keeps the fastest.  The result is cached per (GPU architecture, relax
+ * paths open to the instance, floor(log2 n), floor(log2 max_degree),
+ * field_mode): a later call on a handle of the same class applies the cached shapes without timing
  * (trials = 0).  ASI_TUNE_CACHE=<file> keeps the cache in a text file
  * across processes; ASI_TUNE_NOCACHE=1 always times.  Every trial must reproduce the
  * first trial's flip count and hash, else ASI_ESTATE.  The state, cursor

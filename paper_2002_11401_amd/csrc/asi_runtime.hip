@@ -1302,9 +1302,9 @@ asi_status asi_get_tuning(asi_handle h, asi_tuning* out) {
 }  // extern "C"
 
 // ---- tuning cache: shapes found by asi_tune, keyed by the device
-// architecture and the instance's size class, reused by later asi_tune calls
-// on similar instances (any shapes give the same results; only speed
-// differs).  Optionally persisted in the text file named by ASI_TUNE_CACHE;
+// architecture, the instance's size class and the relax paths open to it, reused
+// by later asi_tune calls on similar instances (any shapes give the same results;
+// only speed differs).  Optionally persisted in the text file named by ASI_TUNE_CACHE;
 // ASI_TUNE_NOCACHE=1 disables lookups.
 namespace {
 
@@ -1340,6 +1340,16 @@ TuneKey tune_key(const asi_sim* h) {
   if (hipGetDeviceProperties(&prop, h->device) == hipSuccess) k.arch = prop.gcnArchName;
   const size_t c = k.arch.find(':');  // feature suffixes (e.g. ":sramecc+") do not matter
   if (c != std::string::npos) k.arch.resize(c);
+  // The relax paths open to the instance, whose limits lie inside the size
+  // classes: the fewest of 4, 8 and 16 wavefronts that hold its keys in LDS (a
+  // class of 10,000 and 16,000 magnets tuned to 4 on the former put the latter on
+  // the max tree), batches by tiles, and whether it may speculate.  It is part of
+  // the first word, so that shapes saved without it are not taken up.
+  int lds = 0;
+  for (int w : {kMaxRelaxWaves, 8, 4})
+    if (relax_keys_in_lds(h->hI, w)) lds = w;
+  k.arch += "/lds" + std::to_string(lds) + (many_fits(h->n, h->D) ? "-tiles" : "") +
+            (h->D <= kSpecMaxD ? "-spec" : "");
   return k;
 }
 
@@ -1540,7 +1550,7 @@ asi_status asi_tune(asi_handle h, int64_t sample_steps, asi_tuning* out) {
     }
   }
   // 2. first-level tile of the max tree
-  for (int dl = 1; st == ASI_OK && dl <= 2; ++dl) {
+  for (int dl = 1; st == ASI_OK && dl <= 2 && !I.lds_keys; ++dl) {
     asi_tuning c = best;
     c.l1_shift = cur.l1_shift + dl;
     st = consider(c);

@@ -49,3 +49,18 @@ def test_threshold_in_force(n, never):
     assert sim.tuning()["spec_min"] == 32
     sim.close()
     assert_same(result(w), result(w, tuning=dict(spec_min=32)))
+
+
+def test_shapes_are_not_carried_over_to_another_path(tmp_path, monkeypatch):
+    """10,000 and 16,000 magnets are of one size class, but 4 wavefronts hold
+    only the former's keys in LDS; the file keeps an entry for each."""
+    monkeypatch.setenv("ASI_TUNE_CACHE", str(tmp_path / "shapes.txt"))
+    sims = [asi.Sim.from_workload(dataclasses.replace(line(n, steps=4), neighbor_distance=70.0))
+            for n in (10000, 16000, 15000)]
+    first, other, same = [s.tune(sample_steps=2) for s in sims]
+    assert first["trials"] > 0 and other["trials"] > 0
+    assert same["trials"] == 0 and same["relax_waves"] == first["relax_waves"]
+    words = (tmp_path / "shapes.txt").read_text().split()
+    assert len(words) == 16 and words[0] != words[8] and words[1:4] == words[9:12]
+    for s in sims:
+        s.close()
