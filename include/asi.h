@@ -193,8 +193,8 @@ asi_status asi_switching_rho(asi_handle a, asi_handle b, double* rho_out, int64_
 
 /* asi_switching_rho for callers that cannot allocate device memory (code
  * under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc): the same rho and sums, bit for bit, with no hipMalloc, hipFree
- * or allocator callback.  Its working memory is one static device array per
+ * hipMalloc): the same rho and sums, bit for bit, with no hipMalloc, hipFree,
+ * hipHostMalloc, hipHostFree or allocator callback.  Its working memory is one static device array per
  * GPU (about 33 MB, held until the process ends), found with
  * hipGetSymbolAddress on the first call on each GPU.  Limits: n in 2 .. 2^20
  * and at most 2^24 flips in each instance's log, else ASI_EINVAL; both

@@ -1166,8 +1166,12 @@ asi_status asi_switching_rho_noalloc(asi_handle a, asi_handle b, double* rho_out
                                 std::to_string(a->n) + "); asi_switching_rho takes up to 2^27");
   const int64_t n = a->n;
   RunDev ra{}, rb{};
-  st = read_run(a, &ra);
-  if (st == ASI_OK) st = read_run(b, &rb);
+  // (not through read_run, which may allocate a pinned buffer)
+  HIPCHK(hipMemcpyAsync(&ra, a->dR, sizeof(RunDev), hipMemcpyDeviceToHost, a->stream), a);
+  st = sync_and_check(a);
+  if (st != ASI_OK) return st;
+  HIPCHK(hipMemcpyAsync(&rb, b->dR, sizeof(RunDev), hipMemcpyDeviceToHost, b->stream), b);
+  st = sync_and_check(b);
   if (st != ASI_OK) return st;
   for (const auto& r : {std::make_pair(a, ra.flips), std::make_pair(b, rb.flips)}) {
     if (r.second > r.first->hI.log_cap)
