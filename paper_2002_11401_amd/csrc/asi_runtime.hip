@@ -15,6 +15,7 @@
 #include <mutex>
 #include <thread>
 #include <tuple>
+#include <utility>
 #include <vector>
 
 #include "../../include/asi.h"
@@ -113,7 +114,7 @@ class HostBuffers {
       if (p) owner->give(p, cap);
     }
   };
-  void take(size_t bytes, Lease& out) {
+  void take(size_t bytes, Lease& out) noexcept {
     size_t cap = kLeast;
     while (cap < bytes) cap <<= 1;
     out.owner = this;
@@ -179,8 +180,10 @@ class HostBuffers {
   size_t kept_ = 0, asked_ = 0;  // asked_: a bit per capacity below kAtOnce
   int64_t handles_ = 0;
 };
-HostBuffers& host_buffers() {
-  static HostBuffers* b = new HostBuffers();  // never destroyed: handles may outlive static objects
+HostBuffers& host_buffers() noexcept {
+  // never destroyed: handles may outlive static objects
+  alignas(HostBuffers) static unsigned char at[sizeof(HostBuffers)];
+  static HostBuffers* b = new (at) HostBuffers();
   return *b;
 }
 
@@ -219,18 +222,18 @@ class Uploads {
   Uploads(const Uploads&) = delete;
   Uploads& operator=(const Uploads&) = delete;
   ~Uploads() {
-    if (!held_.empty()) (void)hipStreamSynchronize(st_);
+    if (count_) (void)hipStreamSynchronize(st_);
   }
-  hipError_t put(void* dst, const void* src, size_t bytes) {
+  hipError_t put(void* dst, const void* src, size_t bytes) noexcept {
     const void* from = src;
     if (bytes <= kPinned) {
-      if (held_.empty() || at_ + bytes > held_.back().cap) {
-        held_.emplace_back();
-        host_buffers().take(std::max(bytes, kBlock), held_.back());
+      const bool room = count_ && at_ + bytes <= held_[count_ - 1].cap;
+      if (!room && count_ < kHeld) {
+        host_buffers().take(std::max(bytes, kBlock), held_[count_++]);
         at_ = 0;
       }
-      if (held_.back().p) {
-        from = std::memcpy(held_.back().p + at_, src, bytes);
+      if (held_[count_ - 1].p && at_ + bytes <= held_[count_ - 1].cap) {
+        from = std::memcpy(held_[count_ - 1].p + at_, src, bytes);
         at_ += (bytes + 63) & ~(size_t)63;
       }
     }
@@ -240,10 +243,15 @@ class Uploads {
  private:
   // small copies share a block (a buffer that is not at hand takes 30-60 us)
   static constexpr size_t kPinned = (size_t)4 << 20, kBlock = (size_t)512 << 10;
+  static constexpr int kHeld = 4;  // buffers a call may hold; then directly
   hipStream_t st_;
   size_t at_ = 0;  // used of the last buffer
-  std::deque<HostBuffers::Lease> held_;
+  int count_ = 0;
+  HostBuffers::Lease held_[kHeld];
 };
+
+// (nothing throws out of a C call, memory run out or not)
+static_assert(noexcept(host_buffers()) && noexcept(std::declval<Uploads&>().put(nullptr, nullptr, 0)));
 
 struct TimerPair {
   hipEvent_t a, b;
@@ -314,6 +322,14 @@ hipEvent_t take_event(asi_sim* s) {
   hipEvent_t e = nullptr;
   if (hipEventCreate(&e) != hipSuccess) return nullptr;
   return e;
+}
+
+void keep_event(asi_sim* s, hipEvent_t e) noexcept {
+  try {
+    s->spare_events.push_back(e);
+  } catch (const std::bad_alloc&) {
+    (void)hipEventDestroy(e);
+  }
 }
 
 // Launch one field pass of the handle's (single) instance.
@@ -422,7 +438,7 @@ bool read_items(asi_sim* s, const void* src, int64_t items, size_t width, F take
     if (st == ASI_OK && e == hipSuccess) take(start(pieces - 1), items, buf.p + start(pieces - 1) * width);
   }
   for (int k = 0; k < pieces; ++k)
-    if (done[k]) s->spare_events.push_back(done[k]);
+    if (done[k]) keep_event(s, done[k]);
   if (e != hipSuccess && st == ASI_OK) {
     s->poisoned = true;
     st = fail(ASI_EDEVICE, std::string("transfer: ") + hipGetErrorString(e));
@@ -995,11 +1011,15 @@ asi_status asi_spin_correlation(asi_handle h, const double* xy, double bin_width
                        dsc + n_bins, h->stream);
     e = hipGetLastError();
   }
-  std::vector<int64_t> sc(2 * (size_t)n_bins);
-  if (e == hipSuccess) rs = read_bytes(h, sc.data(), dsc, 16 * (size_t)n_bins);
-  if (e == hipSuccess && rs == ASI_OK) {
-    std::copy(sc.begin(), sc.begin() + n_bins, sum_out);
-    std::copy(sc.begin() + n_bins, sc.end(), count_out);
+  auto take = [=](int64_t a, int64_t b, const unsigned char* p) {
+    for (int64_t k = a; k < b; ++k)
+      std::memcpy(k < n_bins ? sum_out + k : count_out + (k - n_bins), p + 8 * (k - a), 8);
+  };
+  if (e == hipSuccess && !read_items(h, dsc, 2 * (int64_t)n_bins, 8, take, rs)) {
+    e = hipMemcpyAsync(sum_out, dsc, 8 * (size_t)n_bins, hipMemcpyDeviceToHost, h->stream);
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(count_out, dsc + n_bins, 8 * (size_t)n_bins, hipMemcpyDeviceToHost, h->stream);
+    if (e == hipSuccess) rs = sync_and_check(h);
   }
   if (e != hipSuccess) {
     h->poisoned = true;
