@@ -213,9 +213,10 @@ class Workers {
   std::vector<std::thread> threads_;
 };
 
-// The way up, on one stream: copies up to kPinned bytes pass through pinned
-// buffers (1.4 MB in 70 us; 530 us from pageable memory, which is as fast only
-// from some 3 MB on, where the runtime pins it).  Ends with the stream's end.
+// The way up, on one stream, for calls that a program repeats: copies of kLeast to
+// kMost bytes pass through pinned buffers (1.4 MB in 70 us; 530 us from pageable
+// memory, which is as fast only below some 16 KB and from some 3 MB on, where the
+// runtime pins it).  Ends with the stream's end.
 class Uploads {
  public:
   explicit Uploads(hipStream_t st) : st_(st) {}
@@ -226,26 +227,18 @@ class Uploads {
   }
   hipError_t put(void* dst, const void* src, size_t bytes) noexcept {
     const void* from = src;
-    if (bytes <= kPinned) {
-      const bool room = count_ && at_ + bytes <= held_[count_ - 1].cap;
-      if (!room && count_ < kHeld) {
-        host_buffers().take(std::max(bytes, kBlock), held_[count_++]);
-        at_ = 0;
-      }
-      if (held_[count_ - 1].p && at_ + bytes <= held_[count_ - 1].cap) {
-        from = std::memcpy(held_[count_ - 1].p + at_, src, bytes);
-        at_ += (bytes + 63) & ~(size_t)63;
-      }
+    if (bytes >= kLeast && bytes <= kMost && count_ < kHeld) {
+      HostBuffers::Lease& to = held_[count_++];
+      host_buffers().take(bytes, to);
+      if (to.p) from = std::memcpy(to.p, src, bytes);
     }
     return hipMemcpyAsync(dst, from, bytes, hipMemcpyHostToDevice, st_);
   }
 
  private:
-  // small copies share a block (a buffer that is not at hand takes 30-60 us)
-  static constexpr size_t kPinned = (size_t)4 << 20, kBlock = (size_t)512 << 10;
-  static constexpr int kHeld = 4;  // buffers a call may hold; then directly
+  static constexpr size_t kLeast = (size_t)16 << 10, kMost = (size_t)4 << 20;
+  static constexpr int kHeld = 2;  // buffers a call may hold; then directly
   hipStream_t st_;
-  size_t at_ = 0;  // used of the last buffer
   int count_ = 0;
   HostBuffers::Lease held_[kHeld];
 };
@@ -873,7 +866,7 @@ asi_status asi_set_field_protocol(asi_handle h, int64_t n_steps, const double* h
   h->hI.step_flips = dalloc<int32_t>(h, std::max<int64_t>(1, n_steps));
   if (!h->dH || !h->hI.step_flips) return fail(ASI_ENOMEM, "device allocation failed (protocol)");
   if (n_steps > 0)
-    HIPCHK(Uploads(h->stream).put(h->dH, h_xy, 16 * n_steps), h);
+    HIPCHK(hipMemcpyAsync(h->dH, h_xy, 16 * n_steps, hipMemcpyHostToDevice, h->stream), h);
   HIPCHK(hipMemsetAsync(h->hI.step_flips, 0, 4 * std::max<int64_t>(1, n_steps), h->stream), h);
   h->K = n_steps;
   h->hI.H = h->dH;
@@ -907,7 +900,7 @@ asi_status asi_set_local_field(asi_handle h, int64_t n_slabs, const double* h_lo
   if (n_slabs > 0) {
     h->dHloc = dalloc<double>(h, cnt);
     if (!h->dHloc) return fail(ASI_ENOMEM, "device allocation failed (local field)");
-    HIPCHK(Uploads(h->stream).put(h->dHloc, h_loc, 8 * cnt), h);
+    HIPCHK(hipMemcpyAsync(h->dHloc, h_loc, 8 * cnt, hipMemcpyHostToDevice, h->stream), h);
   }
   h->hI.hloc = reinterpret_cast<const double2*>(h->dHloc);
   h->hI.hloc_k = n_slabs;
@@ -941,7 +934,7 @@ asi_status asi_set_local_wave(asi_handle h, const double* xy, double amp, double
   if (amp != 0.0) {
     h->dWave = dalloc<double>(h, h->n);
     if (!h->dWave) return fail(ASI_ENOMEM, "device allocation failed (wave)");
-    HIPCHK(Uploads(h->stream).put(h->dWave, ph.data(), 8 * h->n), h);
+    HIPCHK(hipMemcpyAsync(h->dWave, ph.data(), 8 * h->n, hipMemcpyHostToDevice, h->stream), h);
     HIPCHK(hipStreamSynchronize(h->stream), h);
   }
   h->hI.wave_ph = h->dWave;
