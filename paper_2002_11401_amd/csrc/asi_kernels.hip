@@ -1021,10 +1021,17 @@ constexpr int kSide = 32;         // side-list entries
 // costs about half a batch per flip on such steps.
 constexpr int kSwitchBatches = 16;
 // Where the one-at-a-time relax holds its keys in LDS, a batch costs about
-// nine of its flips: such a step goes over when four batches in a row commit
-// fewer than nine flips each on average.
+// eight of its flips up to 10,000 magnets and five at 36,000, whose tiles are
+// longer; but a step's batches shrink and grow again, so it goes over when all
+// of its batches so far, four or more, commit fewer flips on average than 7, or
+// 4 above 10,000 magnets at up to 64 neighbours.  (Four batches in a row below
+// nine, as it was: 36,300-magnet kagome at 14 neighbours 2.04 us a flip, 1.11
+// so; 24,300 at 8 neighbours 0.42, 0.25; 36,100-magnet Ising row at 4 2.82,
+// 1.80.  With 4 throughout, 4,800-magnet kagome at 14 and 70 neighbours 1.52
+// and 1.57, with 7 1.30 and 1.43; with 7 throughout the former 1.55 and 2.53.)
 constexpr int kSwitchBatchesLds = 4;
-constexpr double kSwitchFlips = 2.5, kSwitchFlipsLds = 9.0;
+constexpr double kSwitchFlips = 2.5, kSwitchFlipsLds = 7.0, kSwitchFlipsLdsLarge = 4.0;
+constexpr int64_t kSwitchLargeN = 10000;
 // A batch by tiles (relax_many) costs about a flip on the max tree, so those
 // steps stay (36,180-magnet pinwheel at 24 neighbours 2.2 -> 1.4 us a flip).
 // With keys in LDS a flip costs a third of a batch, but a step that starts
@@ -1556,9 +1563,9 @@ __device__ __forceinline__ int relax_spec(const InstDev* __restrict__ I, int64_t
   const bool keys_in_lds = I->lds_keys != 0;
   const int nswitch = keys_in_lds ? kSwitchBatchesLds : kSwitchBatches;
   const double sw = I->spec_switch > 0.0 ? I->spec_switch
-                                         : keys_in_lds ? kSwitchFlipsLds : kSwitchFlips;
-  int64_t flips1 = flips;
-  int nbatch = 0;     // batches since flips1
+                    : !keys_in_lds       ? kSwitchFlips
+                    : I->n > kSwitchLargeN && D <= kManyMaxD ? kSwitchFlipsLdsLarge : kSwitchFlipsLds;
+  int nbatch = 0;
   int set = 0;        // the members' set
   int consumed = 0;   // entries of the last batch that are done with
   unsigned long long committed = 0ull;  // members of the last batch that flipped
@@ -1950,11 +1957,7 @@ __device__ __forceinline__ int relax_spec(const InstDev* __restrict__ I, int64_t
     // batch when every valid member went
     consumed = (pe >= 64 || (valid >> pe) == 0ull) ? B : pe;
     set ^= 1;
-    if (nbatch >= nswitch && (double)(flips - flips1) < sw * nbatch) status = 2;
-    if (keys_in_lds && nbatch == nswitch) {
-      flips1 = flips;
-      nbatch = 0;
-    }
+    if (nbatch >= nswitch && (double)(flips - flips0) < sw * nbatch) status = 2;
     __syncthreads();
     if (status == 2) break;
   }
