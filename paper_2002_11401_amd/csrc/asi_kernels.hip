@@ -78,15 +78,15 @@ __device__ inline void thermal_normals(uint64_t seed, uint32_t i, uint32_t t, do
 }
 
 // Upper bound of x^e (x >= 0, e > 0, x within 2^-22) from the
-// single-precision hardware log2 and exp2: the exponent e log2 x is raised by
-// e 2^-20, past the error of log2 x (x's own, its 24 bits and a few units of
-// the hardware's: below 6e-7, whatever e), and by log2(1.001), far past that
-// of the product and of exp2; x below 2^-100 is raised to 2^-100, which only
-// raises x^e.
+// single-precision hardware log2 and exp2: log2 x is raised by 2^-20, past its
+// error (x's own, its 24 bits and a few units of the hardware's: below 6e-7 for
+// |log2 x| < 4), the exponent by log2(1.001), far past that of a larger
+// |log2 x| (where x^e matters, e |log2 x| < 20, it is below 3e-6), of the product
+// and of exp2; x below 2^-100 is raised to 2^-100, which only raises x^e.
 __device__ inline float pow_bound(double x, double e) {
   const float xf = (float)fmax(x, 0x1p-100), ef = (float)e;
   return __builtin_amdgcn_exp2f(
-      __builtin_fmaf(ef, __builtin_amdgcn_logf(xf), ef * 0x1p-20f + 0.00144197f));
+      __builtin_fmaf(ef, __builtin_amdgcn_logf(xf) + 0x1p-20f, 0.00144197f));
 }
 
 // Switching key: the left-hand side of Eq. 5 when magnet i may flip, i.e.
