@@ -896,6 +896,11 @@ __global__ __launch_bounds__(256) void k_slice_max(const InstDev* __restrict__ i
 // The relax workgroup's dynamic LDS.
 extern __shared__ __align__(16) unsigned char lds_dyn[];
 
+// A part of a relax called out of line.  Each starts on a 256-byte boundary: where
+// the batches by tiles happened to start elsewhere, after changes to other
+// functions, they were 1-2 % slower.
+#define ASI_CALLED __attribute__((noinline, aligned(256)))
+
 // Values that the whole workgroup shares but the compiler cannot know to be
 // the same in every lane (arguments of a function called out of line, values
 // read from LDS); a descriptor, which no kernel writes, also lies in constant
@@ -1476,7 +1481,7 @@ __device__ __forceinline__ int safe_end_wave(const SpecLds& S, const SpecShared&
 __device__ inline uint32_t hash_slot(uint32_t i) { return (i * 2654435761u) >> (32 - 12); }
 
 // Out of line, so that their registers stay out of the batch loop's.
-__device__ __attribute__((noinline)) void call_refill(const InstDev* I, ASI_LDS SpecShared* sh) {
+__device__ ASI_CALLED void call_refill(const InstDev* I, ASI_LDS SpecShared* sh) {
   const SpecLds S = carve_spec(lds_dyn);
   SpecShared& h = *(SpecShared*)sh;
   if (h.ncold > 4 * kWin)
@@ -1485,7 +1490,7 @@ __device__ __attribute__((noinline)) void call_refill(const InstDev* I, ASI_LDS 
     refill(uniform(I), S, h);
 }
 // staging[0, nm) joins the window; what that pushes out joins the pool.
-__device__ __attribute__((noinline)) void call_join(const InstDev* I, ASI_LDS SpecShared* sh, int nm) {
+__device__ ASI_CALLED void call_join(const InstDev* I, ASI_LDS SpecShared* sh, int nm) {
   const SpecLds S = carve_spec(lds_dyn);
   SpecShared& h = *(SpecShared*)sh;
   nm = __builtin_amdgcn_readfirstlane(nm);
@@ -1506,7 +1511,7 @@ __device__ __attribute__((noinline)) void call_join(const InstDev* I, ASI_LDS Sp
   }
   __syncthreads();
 }
-__device__ __attribute__((noinline)) double pow_far(double x, double e) { return pow(x, e); }
+__device__ ASI_CALLED double pow_far(double x, double e) { return pow(x, e); }
 
 // Relax at step t in speculative batches (needs 1024 threads).  flips,
 // logpos and hash are the running counters (hash significant in thread 0).
@@ -3304,10 +3309,10 @@ __device__ __forceinline__ int relax_many(const InstDev* __restrict__ I, int64_t
 }
 
 template <int kRows>
-__device__ __attribute__((noinline)) int call_many(const InstDev* I, int64_t t, ASI_LDS RelaxState* st,
-                                                   int64_t ncand, uint64_t deadline) {
+__device__ ASI_CALLED int call_many(const InstDev* I, int64_t t, ASI_LDS RelaxState* st,
+                                    int64_t ncand, uint64_t deadline) {
   return relax_many<kRows>(uniform(I), uniform(t), *(RelaxState*)st, uniform(ncand),
-                    (uint64_t)uniform((int64_t)deadline));
+                           (uint64_t)uniform((int64_t)deadline));
 }
 
 __device__ __forceinline__ int run_spec(const InstDev* I, int64_t t, RelaxState* st, int64_t ncand,
@@ -3321,8 +3326,8 @@ __device__ __forceinline__ int run_spec(const InstDev* I, int64_t t, RelaxState*
   return status;
 }
 
-__device__ __attribute__((noinline)) int call_spec(const InstDev* I, int64_t t, ASI_LDS RelaxState* st,
-                                                   int64_t ncand, uint64_t deadline) {
+__device__ ASI_CALLED int call_spec(const InstDev* I, int64_t t, ASI_LDS RelaxState* st,
+                                    int64_t ncand, uint64_t deadline) {
   return run_spec(uniform(I), uniform(t), (RelaxState*)st, uniform(ncand),
                   (uint64_t)uniform((int64_t)deadline));
 }
@@ -3341,14 +3346,14 @@ __device__ __forceinline__ int run_tree(const InstDev* I, int64_t t, RelaxState*
 }
 
 template <bool kTile1>
-__device__ __attribute__((noinline)) int call_lds(const InstDev* I, int64_t t, ASI_LDS RelaxState* st,
-                                                  int64_t ncand, bool from_pool, uint64_t deadline) {
+__device__ ASI_CALLED int call_lds(const InstDev* I, int64_t t, ASI_LDS RelaxState* st,
+                                   int64_t ncand, bool from_pool, uint64_t deadline) {
   return relax_lds<kTile1>(uniform(I), uniform(t), lds_dyn, *(RelaxState*)st, uniform(ncand),
                            from_pool, (uint64_t)uniform((int64_t)deadline));
 }
 
 // The field phase of a whole instance by one workgroup.
-__device__ __attribute__((noinline)) void call_field(const InstDev* I0, int64_t t, bool resume) {
+__device__ ASI_CALLED void call_field(const InstDev* I0, int64_t t, bool resume) {
   const InstDev* I = uniform(I0);
   const int wave = threadIdx.x >> 6, NW = blockDim.x >> 6;
   for (int64_t row0 = (int64_t)wave * 64; row0 < I->n; row0 += (int64_t)NW * 64)
