@@ -124,7 +124,7 @@ struct InstDev {
   int64_t ccap;
   int64_t spec_min;       // flippable magnets at step start to go speculative
   double spec_switch;     // mean batch below which a speculative step goes on one flip at a
-                          // time (0: the path's own)
+                          // time (negative: the path's own)
 };
 
 // Per-instance run cursor, device-resident so repeated launches (and

@@ -1567,8 +1567,8 @@ __device__ __forceinline__ int relax_spec(const InstDev* __restrict__ I, int64_t
   const int64_t flips0 = flips;
   const bool keys_in_lds = I->lds_keys != 0;
   const int nswitch = keys_in_lds ? kSwitchBatchesLds : kSwitchBatches;
-  const double sw = I->spec_switch > 0.0 ? I->spec_switch
-                    : !keys_in_lds       ? kSwitchFlips
+  const double sw = I->spec_switch >= 0.0 ? I->spec_switch
+                    : !keys_in_lds        ? kSwitchFlips
                     : I->n > kSwitchLargeN && D <= kManyMaxD ? kSwitchFlipsLdsLarge : kSwitchFlipsLds;
   int nbatch = 0;
   int set = 0;        // the members' set
@@ -2918,7 +2918,7 @@ __device__ __forceinline__ int relax_many(const InstDev* __restrict__ I, int64_t
   ASI_GLOBAL double* const key = I->key;
   ASI_GLOBAL double2* const hh = I->h;
   ASI_GLOBAL double2* const hd = I->hd;
-  const double sw = I->spec_switch > 0.0 ? I->spec_switch : I->lds_keys != 0 ? kManySwitchLds : 0.0;
+  const double sw = I->spec_switch >= 0.0 ? I->spec_switch : I->lds_keys != 0 ? kManySwitchLds : 0.0;
   int64_t done1 = 0;
   int nbatch = 0;
 

@@ -734,7 +734,7 @@ asi_status create_impl(const asi_params* p, const asi_device* dev, asi_sim* s) {
   HIPCHK(hipMemsetAsync(I.ccount, 0, 4, s->stream), s);
   I.spec_min = default_spec_min(I);
   if (const char* e = std::getenv("ASI_SPEC_MIN")) I.spec_min = std::atoll(e);
-  I.spec_switch = 0.0;
+  I.spec_switch = -1.0;
   if (const char* e = std::getenv("ASI_SPEC_SWITCH")) I.spec_switch = std::atof(e);
   // 16 wavefronts: the speculative relax spreads up to 2048 member and
   // neighbour slots over 1024 lanes; touched tiles are rescanned in parallel
