@@ -1020,10 +1020,10 @@ constexpr int kHash = 4096;       // conflict table slots
 constexpr int kMaxPairs = 1024;   // member + neighbour slots per batch: one per thread
 constexpr int kMaxMembers = 64;   // one per lane of the wavefront that chooses them
 constexpr int kSide = 32;         // side-list entries
-// A step whose first kSwitchBatches batches commit fewer than kSwitchFlips
-// (unless spec_switch is given) flips each on average -- an avalanche: every flip
-// makes a neighbour the next candidate -- continues on the max tree, which
-// costs about half a batch per flip on such steps.
+// A step whose batches so far, kSwitchBatches or more, commit fewer than
+// kSwitchFlips (unless spec_switch is given) flips each on average -- an
+// avalanche: every flip makes a neighbour the next candidate -- continues on the
+// max tree, which costs about half a batch per flip on such steps.
 constexpr int kSwitchBatches = 16;
 // Where the one-at-a-time relax holds its keys in LDS, a batch costs about
 // eight of its flips up to 10,000 magnets and five at 36,000, whose tiles are
@@ -1523,10 +1523,10 @@ __device__ ASI_CALLED double pow_far(double x, double e) { return pow(x, e); }
 // members' choice (one wavefront), their rows, their neighbours' fields (in
 // flight while the conflicts are found; one wavefront folds the last batch into
 // the hash meanwhile), the FP64 powers, one to a lane, and the commit: 21,000
-// cycles for 16 members of a 120,000-magnet kagome, 1.16 -> 1.06 us a flip.
-// Against batches of up to 2,048 slots that merged the window each time: 23,000
-// cycles; 1M-magnet kagome 0.46 us a flip in both, a 30,000-magnet kagome at
-// d = 1 0.23 -> 0.20.
+// cycles for 16 members at 32 neighbours.  Against batches of up to 2,048 slots
+// that merged the window each time (23,000 cycles): kagome of 120,000 magnets at
+// 4 neighbours 0.215 -> 0.174 us a flip, of 24,300 0.27 -> 0.23, of 1.2M 0.28 ->
+// 0.25, of 120,000 at 70 neighbours 1.47 -> 1.43.
 __device__ __forceinline__ int relax_spec(const InstDev* __restrict__ I, int64_t t, unsigned char* lds,
                           SpecShared& sh, int64_t ncand, int64_t& flips, int64_t& logpos,
                           uint64_t& hash, uint64_t deadline) {
@@ -2485,16 +2485,16 @@ struct RelaxCount {
 
 // ------------------------------------------------------------ speculative relax, tiles
 // Speculative batches without a sorted window, for up to kManyMaxN magnets and
-// kManyMaxD neighbours: of each tile of 64 consecutive magnets LDS holds the
-// largest key, its place and a bound of the second, and of each of 256 rows of
-// tiles the two largest keys.  The rows' bests that beat every row's second are
+// kManyMinD to kManyMaxD neighbours: of each tile of 64 (128) consecutive magnets
+// LDS holds the largest key, its place and a bound of the second, and of each of
+// 256 (512) rows of tiles the two largest keys.  The rows' bests that beat every row's second are
 // the first magnets of the relax order.
 constexpr int kManyMembers = 32;
 constexpr int kManyHash = 2048;  // conflict table slots (at most 1,056 in use)
 constexpr int kManyList = 1088;  // tiles that a batch changes (at most 1,056)
 // Up to 2^19 magnets tiles of 64 in 256 rows, above tiles of 128 in 512 rows:
-// half the tiles, and twice the rows for the more candidates of such sizes (a
-// 1M-magnet kagome's field window 17.6 ms a pass against 18.0 with 256 rows; a
+// half the tiles, and twice the rows for the more candidates of such sizes (20
+// steps of a 1M-magnet kagome 17.3 ms against 18.0 with 256 rows; a
 // 200,000-magnet square 1.91 us a flip with 256 rows against 2.06).
 constexpr int kManyRows = 256, kManyRowsBig = 512;
 
@@ -2879,7 +2879,7 @@ __device__ __forceinline__ void top2_step(double& m, double& s) {
 // either way).  Below 17 neighbours the window's batches win, which take up to
 // 64 members where this takes 32 (30,000-magnet kagome at 4 neighbours 0.20
 // against 0.46).  Above 2^19 magnets: square at 60 neighbours, 641,000, 2.7 ->
-// 2.2, 1M-magnet kagome reversal 0.94 -> 0.74.
+// 2.2, 1M-magnet kagome reversal 0.94 -> 0.72.
 // Returns as relax_spec.
 template <int kRows>
 __device__ __forceinline__ int relax_many(const InstDev* __restrict__ I, int64_t t, RelaxState& st,

@@ -736,7 +736,7 @@ asi_status create_impl(const asi_params* p, const asi_device* dev, asi_sim* s) {
   if (const char* e = std::getenv("ASI_SPEC_MIN")) I.spec_min = std::atoll(e);
   I.spec_switch = -1.0;
   if (const char* e = std::getenv("ASI_SPEC_SWITCH")) I.spec_switch = std::atof(e);
-  // 16 wavefronts: the speculative relax spreads up to 2048 member and
+  // 16 wavefronts: the speculative relax spreads up to 1024 member and
   // neighbour slots over 1024 lanes; touched tiles are rescanned in parallel
   s->relax_waves = kMaxRelaxWaves;
   if (const char* w = std::getenv("ASI_RELAX_WAVES")) {
